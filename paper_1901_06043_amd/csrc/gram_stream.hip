@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kSNT) void gram_stream_kernel(StreamParams g) {
         const bool cok = rok && c0 < K;
         if (cok) {
           // 16-byte vector loads: base is a multiple of CPL and Y is 16-byte aligned
-          const uint64_t r = c0 / L, l = c0 - r * L;
+          const uint32_t r = (uint32_t)c0 / L, l = (uint32_t)c0 - r * L;  // K < 2^32
           const T* src = Y + ((int64_t)l + JL * (int64_t)r + (int64_t)L * row);
           if constexpr (sizeof(T) == 4) {
 #pragma unroll
@@ -142,15 +142,18 @@ __global__ __launch_bounds__(kSNT) void gram_stream_kernel(StreamParams g) {
           raw[rb][j] = (rok && c < K) ? Y[(int64_t)row + (int64_t)J * (int64_t)c] : (T)0;
         }
       } else {
+        // one division per lane, then the columns are counted up: (r, l) of
+        // column c0 + j (c0 wraps past 2^32 only where no column is read)
+        uint32_t r = (uint32_t)c0 / L, l = (uint32_t)c0 - r * L;
+        const T* src = Y + ((int64_t)l + JL * (int64_t)r + (int64_t)L * row);
 #pragma unroll
         for (int j = 0; j < CPL; ++j) {
-          const uint64_t c = c0 + j;
-          T x = (T)0;
-          if (rok && c < K) {
-            const uint64_t r = c / L, l = c - r * L;
-            x = Y[(int64_t)l + JL * (int64_t)r + (int64_t)L * row];
+          raw[rb][j] = (rok && c0 + j < K) ? *src : (T)0;
+          ++src;
+          if (++l == L) {
+            l = 0;
+            src += JL - L;
           }
-          raw[rb][j] = x;
         }
       }
     }
@@ -300,13 +303,44 @@ __global__ __launch_bounds__(kSNT) void gram_stream_kernel(StreamParams g) {
   }
 }
 
-// Sum the workgroup partials in a fixed order and write both triangles.
-__global__ __launch_bounds__(256) void gram_stream_reduce_kernel(const double* __restrict__ part, int nb,
-                                                                 int64_t nwg, int J, double* __restrict__ S) {
+// Sum the workgroup partials in a fixed order and write both triangles.  A
+// workgroup takes kRE consecutive entries; its kRS thread groups each sum
+// every kRS-th partial (eight loads in flight), then one tree over LDS.  With
+// a single thread per entry the 256 partials of a small Gram were 32 dependent
+// rounds of loads (about 16 us, longer than the Gram itself).  The last
+// workgroup sums the squares (norm2 non-null).
+constexpr int kRE = 32, kRS = 32;
+
+__global__ __launch_bounds__(kRE * kRS) void gram_stream_reduce_kernel(const double* __restrict__ part, int nb,
+                                                                       int64_t nwg, int J,
+                                                                       const double* __restrict__ sq,
+                                                                       double* __restrict__ S,
+                                                                       double* __restrict__ norm2) {
+  __shared__ double sh[kRS][kRE];
   const int nblk = nb * (nb + 1) / 2;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)nblk * 256) return;
-  const int qb = (int)(idx >> 8), rem = (int)(idx & 255);
+  const int tid = threadIdx.x, e = tid & (kRE - 1), u = tid / kRE;
+  if ((int)blockIdx.x == nblk * (256 / kRE)) {
+    double* flat = &sh[0][0];
+    flat[tid] = tid < nwg ? sum_strided8(sq + tid, (nwg - tid + kRE * kRS - 1) / (kRE * kRS), kRE * kRS) : 0.0;
+    __syncthreads();
+    for (int w = kRE * kRS / 2; w > 0; w >>= 1) {
+      if (tid < w) flat[tid] += flat[tid + w];
+      __syncthreads();
+    }
+    if (tid == 0) *norm2 = flat[0];
+    return;
+  }
+  const int idx = (int)blockIdx.x * kRE + e;
+  const int qb = idx >> 8, rem = idx & 255;
+  sh[u][e] = u < nwg ? sum_strided8(part + (int64_t)u * nblk * 256 + idx, (nwg - u + kRS - 1) / kRS,
+                                    (int64_t)kRS * nblk * 256)
+                     : 0.0;
+  __syncthreads();
+  for (int w = kRS / 2; w > 0; w >>= 1) {
+    if (u < w) sh[u][e] += sh[u + w][e];
+    __syncthreads();
+  }
+  if (u != 0) return;
   int bi = 0, qq = qb;
   while (qq >= nb - bi) {
     qq -= nb - bi;
@@ -316,7 +350,7 @@ __global__ __launch_bounds__(256) void gram_stream_reduce_kernel(const double* _
   const int r = rem >> 4, c = rem & 15;
   const int a = 16 * bi + r, b = 16 * bj + c;
   if (a >= J || b >= J || (bi == bj && r > c)) return;
-  const double s = sum_strided8(part + (int64_t)qb * 256 + rem, nwg, (int64_t)nblk * 256);
+  const double s = sh[0][e];
   S[(int64_t)a * J + b] = s;
   S[(int64_t)b * J + a] = s;
 }
@@ -361,9 +395,12 @@ GramPlan plan_gram_stream(int J, uint64_t K, int prec) {
   p.ntiles = (J + 15) / 16;
   p.npairs = p.ntiles * (p.ntiles + 1) / 2;
   p.nchunks = ceil_div((int64_t)K, G);
-  // about 8 waves per SIMD, each with at least 8 column groups
-  const int64_t want = 2048;
-  p.nsplit = std::max<int64_t>(1, std::min<int64_t>(want, ceil_div(p.nchunks, 8 * kSW)));
+  // Up to one workgroup per CU as soon as each wave has a column group: the
+  // 61-row Gram of a 57 x 61 x 43 tensor (154 groups) ran on 5 workgroups of
+  // 8 groups a wave, 33 us against 7.6 us now.  Beyond that, 8 groups per wave up to about 8 waves per
+  // SIMD, so that the partials stay few.
+  p.nsplit = std::max(std::min<int64_t>(256, ceil_div(p.nchunks, kSW)),
+                      std::min<int64_t>(2048, ceil_div(p.nchunks, 8 * kSW)));
   p.cps = ceil_div(p.nchunks, p.nsplit * kSW);
   p.part_elems = p.nsplit * p.npairs * 256;
   p.sq_elems = p.nsplit;
@@ -405,9 +442,8 @@ hipError_t launch_gram_stream(const T* Y, int J, uint64_t L, uint64_t K, int pre
     }
   }
   if (after_main) (void)hipEventRecord(after_main, stream);
-  hipLaunchKernelGGL(gram_stream_reduce_kernel, dim3(ceil_div((int64_t)p.npairs * 256, 256)), dim3(256), 0, stream,
-                     part, nb, p.nsplit, J, S);
-  if (norm2) hipLaunchKernelGGL(sum_fixed_kernel, dim3(1), dim3(256), 0, stream, sq, p.nsplit, norm2);
+  hipLaunchKernelGGL(gram_stream_reduce_kernel, dim3(p.npairs * (256 / kRE) + (norm2 ? 1 : 0)), dim3(kRE * kRS), 0,
+                     stream, part, nb, p.nsplit, J, sq, S, norm2);
   return hipGetLastError();
 }
 
