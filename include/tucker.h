@@ -338,7 +338,8 @@ typedef enum {
 /* Statistics of the I_n hyperslices of mode n of X (device, natural
  * descending, `dtype`): stats (device) receives TUCKER_NSTATS x I_n doubles,
  * stats[s * I_n + i] for statistic s of slice i.  Accumulated in FP64 in a
- * fixed order (two passes over X: the mean first).  Asynchronous. */
+ * fixed order (one pass over X; the deviations are taken from the means of
+ * small batches and merged).  Asynchronous. */
 tucker_status tucker_slice_stats(const void* X, tucker_dtype dtype, const int64_t* dims, int N, int n,
                                  double* stats, hipStream_t stream);
 

@@ -766,10 +766,10 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
         TmpBuf work;
         HIP_TRY(work.alloc(sizeof(double) * tk::slice_stats_work_doubles(L, J, Rt), stream));
         if (ydt == TUCKER_F64)
-          HIP_TRY(tk::launch_slice_stats(static_cast<const double*>(Y), L, J, Rt, false, work.as<double>(),
+          HIP_TRY(tk::launch_slice_stats(static_cast<const double*>(Y), L, J, Rt, work.as<double>(),
                                          stats.as<double>(), stream));
         else
-          HIP_TRY(tk::launch_slice_stats(static_cast<const float*>(Y), L, J, Rt, false, work.as<double>(),
+          HIP_TRY(tk::launch_slice_stats(static_cast<const float*>(Y), L, J, Rt, work.as<double>(),
                                          stats.as<double>(), stream));
         HIP_TRY(tk::launch_slice_pow2(stats.as<double>(), J, pscale.as<double>(), stream));
         HIP_TRY(tk::launch_fill(zero.as<double>(), J, 0.0, stream));
@@ -1436,10 +1436,10 @@ tucker_status tucker_slice_stats(const void* X, tucker_dtype dtype, const int64_
   TmpBuf work;
   HIP_TRY(work.alloc(sizeof(double) * tk::slice_stats_work_doubles(L, dims[n], Rt), stream));
   if (dtype == TUCKER_F64)
-    HIP_TRY(tk::launch_slice_stats(static_cast<const double*>(X), L, dims[n], Rt, true, work.as<double>(), stats,
+    HIP_TRY(tk::launch_slice_stats(static_cast<const double*>(X), L, dims[n], Rt, work.as<double>(), stats,
                                    stream));
   else
-    HIP_TRY(tk::launch_slice_stats(static_cast<const float*>(X), L, dims[n], Rt, true, work.as<double>(), stats,
+    HIP_TRY(tk::launch_slice_stats(static_cast<const float*>(X), L, dims[n], Rt, work.as<double>(), stats,
                                    stream));
   return TUCKER_OK;
 }

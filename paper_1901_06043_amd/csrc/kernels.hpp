@@ -222,12 +222,12 @@ hipError_t launch_ttm_batched(const TtmBatch& b, bool fp32_products, bool unit_l
 
 // ---------------------------------------------------------------- hyperslices (slice.hip)
 // Statistics of the J slices of mode n (geometry L, J, Rt): stats[s*J + a]
-// for s = mean, std, min, max, 1-norm, 2-norm; the standard deviation (second
-// pass) only if both_passes.  work: slice_stats_work_doubles doubles.
+// for s = mean, std, min, max, 1-norm, 2-norm.  work: slice_stats_work_doubles
+// doubles.
 int64_t slice_stats_work_doubles(uint64_t L, uint64_t J, uint64_t Rt);
 template <typename T>
-hipError_t launch_slice_stats(const T* Y, uint64_t L, uint64_t J, uint64_t Rt, bool both_passes, double* work,
-                              double* stats, hipStream_t s);
+hipError_t launch_slice_stats(const T* Y, uint64_t L, uint64_t J, uint64_t Rt, double* work, double* stats,
+                              hipStream_t s);
 // shift/scale from stats: method 0 standardization, 1 max rescaling (a zero scale becomes 1).
 hipError_t launch_scaling_vectors(const double* stats, uint64_t J, int method, double* shift, double* scale,
                                   hipStream_t s);

@@ -1,0 +1,84 @@
+"""GPU kernels at the edges of the splits that their launches choose: workgroup
+counts, remainders, aligned and unaligned loads, against the FP64 CPU oracle.
+
+Tolerances: sums of n values in FP64 in another order differ by at most about
+n u sum|x|, taken as 1e-12 (statistics) and 1e-11 sqrt(S_aa S_bb) (Grams), as in
+the parity tests.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def tk():
+    import paper_1901_06043_amd as tk
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    tk.lib()
+    return tk
+
+
+def to_dev(x, dims, dtype):
+    return torch.from_numpy(np.ascontiguousarray(x).reshape(list(reversed(dims)))).to("cuda", dtype)
+
+
+# columns of the mode: one group of 16, a group and a column, one workgroup's
+# four groups and their neighbours, around 256 workgroups of four groups, and
+# past 8192 groups, where the waves take several groups each
+@pytest.mark.parametrize("J", [1, 16, 17, 33, 61, 64])
+@pytest.mark.parametrize("cols", [1, 16, 17, 63, 64, 65, 16383, 16385, 131073])
+def test_small_mode_gram_splits(tk, orc, J, cols):
+    rng = np.random.default_rng(J * 1000 + cols)
+    for dims, n in (([J, cols], 0), ([cols, J], 1), ([3, J, -(-cols // 3)], 1)):
+        X = rng.standard_normal(int(np.prod(dims)))
+        S, nrm = tk.gram(to_dev(X, dims, torch.float64), n, dims=dims, with_norm=True)
+        ref = orc.gram(X, dims, n)
+        d = np.sqrt(np.outer(np.diag(ref), np.diag(ref)))
+        assert np.all(np.abs(S.cpu().numpy() - ref) <= 1e-11 * d), (dims, n)
+        assert abs(float(nrm[0]) - np.dot(X, X)) <= 1e-12 * np.dot(X, X)
+
+
+# row mapping with 16-byte and scalar loads, ragged batches of 16; period
+# mapping with 1 .. 512 periods per group, incomplete groups and batches
+@pytest.mark.parametrize("dims,n", [
+    ([64, 5, 3], 1), ([66, 5, 3], 1), ([65, 3, 31], 1), ([4096, 2, 9], 1), ([128, 40], 1), ([1500, 3], 0),
+    ([2, 4100], 0), ([2, 4097], 0), ([7, 1000], 0), ([1, 8, 999], 1), ([3, 5, 70], 1), ([31, 33, 10], 1),
+    ([513, 77], 0), ([1024, 17], 0), ([2, 1], 0),
+])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_slice_stats_edges(tk, orc, dims, n, dtype, offset):
+    rng = np.random.default_rng(sum(dims) + n)
+    size = int(np.prod(dims))
+    X = (rng.standard_normal(size) * 2.0 + 1.0e3).astype(dtype)
+    tdt = torch.float64 if dtype == np.float64 else torch.float32
+    buf = torch.empty(size + offset, dtype=tdt, device="cuda")
+    buf[offset:] = torch.from_numpy(X)
+    st = tk.slice_stats(buf[offset:], n, dims=dims).cpu().numpy()
+    ref = orc.slice_stats(X.astype(np.float64), dims, n)
+    cnt = size // dims[n]
+    np.testing.assert_array_equal(st[2:4], ref[2:4])
+    assert np.all(np.abs(st[0] - ref[0]) <= 1e-12 * ref[4] / cnt)
+    assert np.all(np.abs(st[1] - ref[1]) <= 1e-12 * ref[5] / np.sqrt(cnt))
+    np.testing.assert_allclose(st[4:], ref[4:], rtol=1e-12)
+
+
+@pytest.mark.parametrize("dims,n", [([4, 3, 700], 1), ([640, 3, 5], 1)])
+def test_slice_stats_special_values(tk, dims, n):
+    """A constant slice has no deviation; one infinity or NaN stays in its slice."""
+    size = int(np.prod(dims))
+    rng = np.random.default_rng(3)
+    X = rng.standard_normal(size).reshape(list(reversed(dims)))
+    v = np.moveaxis(X, len(dims) - 1 - n, 0)
+    v[0] = 0.1
+    v[1].flat[7] = np.inf
+    st = tk.slice_stats(to_dev(X.reshape(-1), dims, torch.float64), n, dims=dims).cpu().numpy()
+    assert st[1][0] <= 1e-15 and st[2][0] == st[3][0] == 0.1
+    assert st[0][1] == np.inf and np.isnan(st[1][1]) and st[3][1] == np.inf and st[5][1] == np.inf
+    np.testing.assert_allclose(st[1][2], v[2].std(), rtol=1e-12)
+    v[1].flat[7] = np.nan
+    st = tk.slice_stats(to_dev(X.reshape(-1), dims, torch.float64), n, dims=dims).cpu().numpy()
+    assert np.isnan(st[0][1]) and np.isnan(st[1][1]) and np.isfinite(st[3][1])
