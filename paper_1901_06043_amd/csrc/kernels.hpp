@@ -93,12 +93,18 @@ __global__ void sum_fixed_kernel(const double* __restrict__ x, int64_t n, double
 // Z_(n) = M Y_(n);  M is K x J with element (k,j) at M[k*msk + j*msj].
 // fp32_products: FP32 MFMA products (M and Y rounded to FP32), else FP64.
 // FP64 mode product for more than 64 output rows with direct global-to-LDS
-// staging (ttm_dma.hip): M with contiguous rows (msj = 1) or columns
-// (msk = 1) and even stride, 16-byte aligned M and Y; L = 1 needs double Y
-// and even J, L > 1 needs L a multiple of 16 / sizeof(TI); float Y only with
-// contiguous rows of M and double output.  launch_ttm uses it when eligible.
-bool ttm_dma_eligible(int J, uint64_t L, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, int zsize,
-                      const void* Y, const void* M);
+// staging (ttm_dma.hip): M with contiguous rows (msj = 1) or, for double Y,
+// columns (msk = 1) and even stride, 16-byte aligned; any Y and output of
+// float or double.  launch_ttm uses it when eligible.
+bool ttm_dma_eligible(int J, uint64_t L, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
+                      const void* M);
+// True where only the layout of M stands in the way: a copy P (K x ld, rows
+// contiguous, ld >= J even, 16-byte aligned) made by launch_pack_factor is
+// taken.
+bool ttm_dma_wants_pack(int J, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
+                        const void* M);
+hipError_t launch_pack_factor(const double* M, int64_t msk, int64_t msj, int K, int J, int ld, double* P,
+                              hipStream_t stream);
 // Output of a mode product (L > 1) whose L covers a mode p of extent Pp on
 // input and Rp on output: l = a + Lp (i_p + Pp h) on input is written to
 // a + Lp (i_p + Rp h).  Rp < Pp drops the zero slices i_p >= Rp of a padded

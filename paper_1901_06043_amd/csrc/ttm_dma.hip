@@ -49,7 +49,8 @@ struct TtmDmaParams {
 // ORI 0 (L > 1): A = M (row form MF = 0, column form MF = 1), B = Y (column
 // form).  ORI 1 (L = 1): A = Y (row form), B = M.
 // WY: bytes per lane of the Y loads, 16, or 4 where Y's rows or columns are
-// only 8-byte aligned (odd L or J); M is always loaded in 16-byte units.
+// not 16-byte aligned (L or J odd, or not a multiple of 4 for floats); M is
+// always loaded in 16-byte units (launch_pack_factor makes an aligned copy).
 template <typename TY, int ORI, int MF, int WY>
 struct Cfg {
   using IM = TImg<MF == 0 ? 0 : 1, 8>;
@@ -57,7 +58,6 @@ struct Cfg {
   static constexpr int MB = IM::BYTES, YB = IY::BYTES;
   static constexpr int BUF = MB + YB;  // one chunk: M image then Y image
   static constexpr int NIM = MB / 1024, NIY = YB / (64 * WY);  // load instructions per image
-  static_assert(WY == 16 || sizeof(TY) == 8, "4-byte loads for double input only");
 };
 
 // Per-lane state of the loads of one item (tile at output row k0, column
@@ -71,6 +71,9 @@ struct Cfg {
 //     the lane's rows alternate between two sets with the swizzle of j (bit 1
 //     of n); row form, 2 rows per instruction (8 more per n) and the lane's j
 //     alternate between two values with the row pair's swizzle (bit 0 of n).
+//     Floats: column form, j = 2 n + (w >> 1) and the lane's rows take four
+//     sets (n & 3); row form, 4 rows per instruction (16 more per n) and one
+//     j per lane.
 template <typename TY, int ORI, int MF, int WY>
 struct Loader {
   const char* mlane;   // M(k0 + mrow0, 0)
@@ -79,6 +82,7 @@ struct Loader {
   const char* ycol1;   // and for the other swizzle pattern
   int64_t mjstride;    // M bytes per reduction index j
   int64_t yjstride;    // Y bytes per j
+  const char* ycolf[4];  // 4-byte column form of floats: the four swizzle patterns
   int64_t c0;
   int k0, mrow0, yrow0;
   int yr0, yr1, yj0, yj1;  // 4-byte loads: rows (column form) or j (row form) per pattern
@@ -99,8 +103,8 @@ __device__ __forceinline__ void loader_init(Loader<TY, ORI, MF, WY>& ld, const T
   // column c of the unfolding sits at l + L J m (clamped into the tensor;
   // lanes past the end issue nothing)
   auto colbase = [&](int rr) {
-    const int64_t c = min(c0 + rr, g.cols - 1);
-    const int64_t m = c / g.L, l = c - m * g.L;
+    const uint32_t c = (uint32_t)min(c0 + rr, g.cols - 1);  // cols < 2^32
+    const uint32_t m = c / (uint32_t)g.L, l = c - m * (uint32_t)g.L;
     return g.Y + (l + g.L * (int64_t)g.J * m) * (int64_t)sizeof(TY);
   };
   if constexpr (WY == 16) {
@@ -108,6 +112,16 @@ __device__ __forceinline__ void loader_init(Loader<TY, ORI, MF, WY>& ld, const T
     ld.yrow0 = r;
     if constexpr (ORI == 0) ld.ylane = colbase(r);
     else ld.ylane = g.Y + min(c0 + r, g.cols - 1) * g.J * (int64_t)sizeof(TY);
+  } else if constexpr (sizeof(TY) == 4 && ORI == 0) {
+    // column form, 512 bytes per j: instruction w + 4 n covers half w & 1 of j
+    ld.yr0 = 4 * (16 * (wave & 1) + (lane >> 2)) + (lane & 3);  // pattern p: rows ^ 16 p
+#pragma unroll
+    for (int p = 0; p < 4; ++p) ld.ycolf[p] = colbase(ld.yr0 ^ (16 * p));
+  } else if constexpr (sizeof(TY) == 4) {
+    // row form, 4 rows of 64 bytes per instruction: rows 4 w + 16 n + (lane >> 4)
+    ld.yrow0 = 4 * wave + (lane >> 4);
+    ld.ylane = g.Y + min(c0 + ld.yrow0, g.cols - 1) * g.J * (int64_t)sizeof(TY);
+    ld.yj0 = 4 * (((lane & 15) >> 2) ^ wave) + (lane & 3);
   } else if constexpr (ORI == 0) {
     // column form, 1024 bytes per j: instruction w + 4 n covers quarter w of j = n
     const int u = 16 * wave + (lane >> 2);
@@ -155,6 +169,19 @@ __device__ __forceinline__ void issue_chunk(const Loader<TY, ORI, MF, WY>& ld, c
         const char* src = ld.ylane + row_off + (int64_t)(j0 + j) * ld.yjstride;
         __builtin_amdgcn_global_load_lds(static_cast<const void*>(src), (lds_void*)(buf + C::MB + jj * 1024), 16,
                                          0, 0);
+      }
+    }
+  } else if constexpr (sizeof(TY) == 4) {
+    // 4-byte loads of floats, 8 instructions per wave
+#pragma unroll
+    for (int n = 0; n < C::NIY / kTDW; ++n) {
+      const int jj = wave + kTDW * n;
+      const int r = (ORI == 0) ? (ld.yr0 ^ (16 * (n & 3))) : ld.yrow0 + 16 * n;
+      const int j = (ORI == 0) ? 2 * n + (wave >> 1) : ld.yj0;
+      if (ld.c0 + r < g.cols && j0 + j < g.J) {
+        const char* src = (ORI == 0) ? ld.ycolf[n & 3] : ld.ylane + (int64_t)(16 * n) * g.J * 4;
+        __builtin_amdgcn_global_load_lds(static_cast<const void*>(src + (int64_t)(j0 + j) * ld.yjstride),
+                                         (lds_void*)(buf + C::MB + jj * 256), 4, 0, 0);
       }
     }
   } else {
@@ -216,29 +243,31 @@ __device__ __forceinline__ void fill_chunk(const Loader<TY, ORI, MF, WY>& ld, co
       for (int h = 0; h < 16 / ES; ++h)
         if (j0 + j + (ORI == 1 ? h : 0) >= g.J) e[h] = (TY)0;
     } else {
-      const int jl = (ORI == 0) ? n : ((n & 1) ? ld.yj1 : ld.yj0);
+      const int jl = (ES == 4) ? (ORI == 0 ? 2 * n + (wave >> 1) : ld.yj0)
+                               : (ORI == 0 ? n : ((n & 1) ? ld.yj1 : ld.yj0));
       if (j0 + jl >= g.J) *reinterpret_cast<uint32_t*>(buf + C::MB + jj * 256 + lane * 4) = 0u;
     }
   }
 }
 
 // Operand reads of one lane for its four blocks (16 rows each) of an image,
-// one step ahead of the MFMAs.  Row form: one 16-byte unit per block serves
+// one step ahead of the MFMAs.  Row form: one pair of values per block serves
 // steps 2 g and 2 g + 1, at o[x] (g = 0) or o[x] + d (g = 1); column form:
 // step s at o[x] + (s & 1) CB + 8 (s >> 1) CB.
 template <int FORM, typename T>
 struct Opnd;
 
 template <typename T>
-struct Opnd<0, T> {  // row form (doubles)
-  double2 u[4];
+struct Opnd<0, T> {  // row form
+  typedef T pair __attribute__((ext_vector_type(2)));
+  pair u[4];
   __device__ __forceinline__ void fetch(const char* img, const int (&o)[4], int d, int s) {
     if ((s & 1) == 0) {
 #pragma unroll
-      for (int x = 0; x < 4; ++x) u[x] = *reinterpret_cast<const double2*>(img + o[x] + (s ? d : 0));
+      for (int x = 0; x < 4; ++x) u[x] = *reinterpret_cast<const pair*>(img + o[x] + (s ? d : 0));
     }
   }
-  __device__ __forceinline__ double get(int x, int s) const { return (s & 1) ? u[x].y : u[x].x; }
+  __device__ __forceinline__ double get(int x, int s) const { return (double)((s & 1) ? u[x].y : u[x].x); }
 };
 
 template <typename T>
@@ -328,12 +357,12 @@ __device__ __forceinline__ void store_tile(const TtmDmaParams& g, const d4 (&acc
     for (int y = 0; y < 4; ++y) {
       const int64_t c = c0l + 16 * (b0 + y) + i;
       if (c >= g.cols) continue;
-      const int64_t m = c / g.L, l = c - m * g.L;
+      const int64_t m = (uint32_t)c / (uint32_t)g.L, l = c - m * g.L;  // cols < 2^32
       int64_t lo = l;
       bool zpad = false;  // also write the appended zero slice after this one
       if (g.Pp != g.Rp) {  // uniform
-        const int64_t t = l / g.Lp, a = l - t * g.Lp;
-        const int64_t h = t / g.Pp, ip = t - h * g.Pp;
+        const int64_t t = (uint32_t)l / (uint32_t)g.Lp, a = l - t * g.Lp;
+        const int64_t h = (uint32_t)t / (uint32_t)g.Pp, ip = t - h * g.Pp;
         if (ip >= g.Rp) continue;  // a zero slice of the padded mode
         lo = a + g.Lp * (ip + g.Rp * h);
         zpad = g.Rp > g.Pp && ip == g.Pp - 1;
@@ -454,34 +483,65 @@ __global__ __launch_bounds__(kTDNT, 2) void ttm_dma_kernel(TtmDmaParams g) {
 }  // namespace
 
 // 16-byte loads of Y need its rows (L = 1: stride J) or slabs (L > 1: the
-// element offset L j) 16-byte aligned; otherwise double input takes 4-byte
-// loads.
+// element offset L j) 16-byte aligned; otherwise it takes 4-byte loads.
 static bool ttm_dma_y16(int J, uint64_t L, int ysize, const void* Y) {
   if (reinterpret_cast<uintptr_t>(Y) % 16) return false;
   if (L == 1) return ((uint64_t)J * ysize) % 16 == 0;
   return L % (16 / ysize) == 0;
 }
 
-bool ttm_dma_eligible(int J, uint64_t L, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, int zsize,
-                      const void* Y, const void* M) {
+// M is read in 16-byte units: rows contiguous (msj = 1, row stride a multiple
+// of 16 bytes) or columns contiguous (msk = 1, column stride likewise; double
+// Y only).
+static bool ttm_dma_m16(int64_t msk, int64_t msj, int ysize, const void* M) {
+  if (reinterpret_cast<uintptr_t>(M) % 16) return false;
+  return (msj == 1 && msk % 2 == 0) || (ysize == 8 && msk == 1 && msj % 2 == 0);
+}
+
+bool ttm_dma_eligible(int J, uint64_t L, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
+                      const void* M) {
+  (void)L;
   if (K <= 64 || J < 16 || cols == 0) return false;
-  if (reinterpret_cast<uintptr_t>(M) % 16 || reinterpret_cast<uintptr_t>(Y) % ysize) return false;
-  // M: rows contiguous (msj = 1, row stride a multiple of 16 bytes) or
-  // columns contiguous (msk = 1, column stride likewise)
-  const bool mrow = (msj == 1 && msk % 2 == 0), mcol = (msk == 1 && msj % 2 == 0);
-  if (!mrow && !mcol) return false;
-  if (ysize == 4) {
-    // float input: 16-byte loads only, slabs of L > 1, the factor of a
-    // compression (rows of M contiguous) and double output
-    return L > 1 && ttm_dma_y16(J, L, ysize, Y) && mrow && zsize == 8;
+  return ttm_dma_m16(msk, msj, ysize, M) && reinterpret_cast<uintptr_t>(Y) % ysize == 0;
+}
+
+bool ttm_dma_wants_pack(int J, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
+                        const void* M) {
+  if (K <= 64 || J < 16 || cols == 0 || reinterpret_cast<uintptr_t>(Y) % ysize) return false;
+  return !ttm_dma_m16(msk, msj, ysize, M);
+}
+
+// P(k, j) = M(k, j) for j < J, zero for J <= j < ld, at P[k * ld + j].  Tiles
+// of 32 x 32 through LDS, so that both sides run along their contiguous axis.
+__global__ __launch_bounds__(256) void pack_factor_kernel(const double* __restrict__ M, int64_t msk, int64_t msj,
+                                                          int K, int J, int ld, double* __restrict__ P) {
+  __shared__ double t[32][33];
+  const int k0 = 32 * blockIdx.y, j0 = 32 * blockIdx.x;
+  const int u = threadIdx.x & 31, v = threadIdx.x >> 5;
+  const bool alongk = msk < msj;
+#pragma unroll
+  for (int p = 0; p < 32; p += 8) {
+    const int k = alongk ? u : v + p, j = alongk ? v + p : u;
+    t[k][j] = (k0 + k < K && j0 + j < J) ? M[(int64_t)(k0 + k) * msk + (int64_t)(j0 + j) * msj] : 0.0;
   }
-  return true;
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < 32; p += 8)
+    if (k0 + v + p < K && j0 + u < ld) P[(int64_t)(k0 + v + p) * ld + j0 + u] = t[v + p][u];
+}
+
+hipError_t launch_pack_factor(const double* M, int64_t msk, int64_t msj, int K, int J, int ld, double* P,
+                              hipStream_t stream) {
+  if (ld < J || K < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(pack_factor_kernel, dim3(ceil_div(ld, 32), ceil_div(K, 32)), dim3(256), 0, stream, M, msk, msj,
+                     K, J, ld, P);
+  return hipGetLastError();
 }
 
 template <typename TY, typename TZ>
 hipError_t launch_ttm_dma(const TY* Y, int J, uint64_t L, uint64_t cols, const double* M, int64_t msk, int64_t msj,
                           int K, TZ* Z, hipStream_t stream, const TtmOutRemap& rm) {
-  if (!ttm_dma_eligible(J, L, cols, K, msk, msj, (int)sizeof(TY), (int)sizeof(TZ), Y, M))
+  if (!ttm_dma_eligible(J, L, cols, K, msk, msj, (int)sizeof(TY), Y, M) || cols >= (uint64_t(1) << 32))
     return hipErrorInvalidValue;
   const bool remap = rm.Pp != rm.Rp;
   if (remap && (L == 1 || rm.Lp < 1 || rm.Rp < 1 || rm.Rp > rm.Pp + 1 || (int64_t)L % (rm.Lp * rm.Pp) != 0))
@@ -505,27 +565,19 @@ hipError_t launch_ttm_dma(const TY* Y, int J, uint64_t L, uint64_t cols, const d
   const int64_t grid = ceil_div(g.total, kXcds) * kXcds;
   const bool mrow = (msj == 1 && msk % 2 == 0);
   const bool y16 = ttm_dma_y16(J, L, (int)sizeof(TY), Y);
-#define TDMA(TYV, ORI, MF, WYV) \
-  hipLaunchKernelGGL((ttm_dma_kernel<TYV, TZ, ORI, MF, WYV>), dim3(grid), dim3(kTDNT), 0, stream, g)
-#define TDMA_W(ORI, MF)               \
-  do {                                \
-    if (y16) TDMA(double, ORI, MF, 16); \
-    else TDMA(double, ORI, MF, 4);      \
+#define TDMA_W(ORI, MF)                                                                                             \
+  do {                                                                                                              \
+    if (y16) hipLaunchKernelGGL((ttm_dma_kernel<TY, TZ, ORI, MF, 16>), dim3(grid), dim3(kTDNT), 0, stream, g);      \
+    else hipLaunchKernelGGL((ttm_dma_kernel<TY, TZ, ORI, MF, 4>), dim3(grid), dim3(kTDNT), 0, stream, g);           \
   } while (0)
-  if constexpr (std::is_same<TY, float>::value) {
-    if constexpr (std::is_same<TZ, double>::value) TDMA(float, 0, 0, 16);
-    else return hipErrorInvalidValue;  // excluded by ttm_dma_eligible
-  } else {
-    if (L == 1) {
-      if (mrow) TDMA_W(1, 0);
-      else TDMA_W(1, 1);
-    } else {
-      if (mrow) TDMA_W(0, 0);
-      else TDMA_W(0, 1);
-    }
+  if (mrow) {
+    if (L == 1) TDMA_W(1, 0);
+    else TDMA_W(0, 0);
+  } else if constexpr (std::is_same<TY, double>::value) {
+    if (L == 1) TDMA_W(1, 1);
+    else TDMA_W(0, 1);
   }
 #undef TDMA_W
-#undef TDMA
   return hipGetLastError();
 }
 

@@ -1,0 +1,106 @@
+"""FP64 mode products over every layout of the operands that the direct-load
+kernel takes, itself or through an aligned copy of the factor, against numpy
+in FP64.
+
+Tolerance: a sum of J products in another order differs by at most about
+J u |M||Y| (1e-12 of it here), plus one rounding of a float32 output.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def tk():
+    import paper_1901_06043_amd as tk
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    tk.lib()
+    return tk
+
+
+def check(tk, dims, n, K, layout, ydt, zdt, offset=0):
+    rng = np.random.default_rng(sum(dims) + K)
+    shape = list(reversed(dims))
+    Y = rng.standard_normal(shape).astype(ydt)
+    M = rng.standard_normal((K, dims[n]))
+    t = {np.float32: torch.float32, np.float64: torch.float64}
+    buf = torch.empty(Y.size + offset, dtype=t[ydt], device="cuda")
+    buf[offset:] = torch.from_numpy(Y.reshape(-1))
+    if layout == "rows":
+        m = torch.from_numpy(M).cuda()
+    elif layout == "columns":
+        m = torch.from_numpy(np.ascontiguousarray(M.T)).cuda().t()
+    else:  # every other column of a wider matrix
+        wide = torch.zeros((K, 2 * dims[n]), dtype=torch.float64, device="cuda")
+        wide[:, ::2] = torch.from_numpy(M)
+        m = wide[:, ::2]
+    z = tk.ttm(buf[offset:].view(shape), n, m, dims=dims, out_dtype=t[zdt]).cpu().numpy()
+    ax = len(dims) - 1 - n
+    ref = np.moveaxis(np.tensordot(M, Y.astype(np.float64), axes=([1], [ax])), 0, ax)
+    mag = np.moveaxis(np.tensordot(np.abs(M), np.abs(Y).astype(np.float64), axes=([1], [ax])), 0, ax)
+    assert z.dtype == zdt
+    tol = 1e-12 * mag + (2.0 ** -23 * np.abs(ref) if zdt == np.float32 else 0.0)
+    assert np.all(np.abs(z - ref) <= tol), (dims, n, K, layout)
+
+
+# L = 1 and L > 1; strides that are 0, 1, 2, 3 modulo 4 (16-byte, 4-byte
+# loads); one chunk, a ragged last chunk of at most and of more than 8 indices;
+# one, several and ragged row tiles; few and ragged columns
+SHAPES = [
+    ([16, 131], 0, 65), ([17, 130], 0, 129), ([18, 300], 0, 200), ([19, 129], 0, 65), ([40, 9, 15], 0, 90),
+    ([4, 33, 40], 1, 66), ([5, 24, 30], 1, 65), ([6, 41, 30], 1, 130), ([131, 47], 1, 301), ([128, 64, 2], 1, 65),
+    ([63, 313, 3], 1, 235), ([3, 7, 16], 2, 70),
+]
+
+
+@pytest.mark.parametrize("dims,n,K", SHAPES)
+@pytest.mark.parametrize("layout", ["rows", "columns", "strided"])
+def test_ttm_layouts(tk, dims, n, K, layout):
+    for ydt in (np.float64, np.float32):
+        for zdt in (np.float64, np.float32):
+            check(tk, dims, n, K, layout, ydt, zdt)
+    # one element past an aligned address: 4-byte loads
+    check(tk, dims, n, K, layout, np.float32, np.float64, offset=1)
+    check(tk, dims, n, K, layout, np.float64, np.float64, offset=1)
+
+
+def test_ttm_capture_odd_factor(tk):
+    """A captured product whose factor is not in 16-byte units allocates nothing and replays."""
+    rng = np.random.default_rng(0)
+    y = torch.from_numpy(rng.standard_normal((30, 41, 12))).cuda()
+    m = torch.from_numpy(rng.standard_normal((70, 41))).cuda()
+    want = tk.ttm(y, 1, m)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        z = tk.ttm(y, 1, m)
+    for s in (1.0, 2.0):
+        y.mul_(s)
+        g.replay()
+        torch.cuda.synchronize()
+        torch.testing.assert_close(z, s * want, rtol=1e-12, atol=1e-12)
+
+
+# odd mode sizes and ranks: factors that are copied, a zero slice appended to
+# an odd mode 0, ranges that begin at an odd row
+@pytest.mark.parametrize("dims,ranks", [([131, 90, 77], [65, 67, 66]), ([200, 75, 101], [17, 66, 65])])
+def test_odd_factors_whole_path(tk, orc, dims, ranks):
+    rng = np.random.default_rng(5)
+    X = rng.standard_normal(int(np.prod(dims)))
+    x = torch.from_numpy(X.reshape(list(reversed(dims)))).cuda()
+    for order in ([2, 0, 1], [0, 1, 2]):
+        t = tk.sthosvd_ranks(x, ranks, mode_order=order)
+        ref = orc.sthosvd(X, dims, 0.0, order, ranks=ranks)
+        assert t.ranks == list(ref.ranks)
+        full, _ = orc.reconstruct(ref, [0, 0, 0], dims)
+        got = t.reconstruct().cpu().numpy().reshape(-1)
+        assert np.abs(got - full).max() <= 1e-9 * np.abs(full).max()
+        b, e = [1, 3, 5], dims
+        part, _ = orc.reconstruct(ref, b, e)
+        for dt, tol in ((torch.float64, 1e-9), (torch.float32, 1e-6)):
+            got = t.reconstruct(b, e, out_dtype=dt).cpu().numpy().reshape(-1)
+            assert np.abs(got - part).max() <= tol * np.abs(part).max()
+        t.free()
