@@ -65,13 +65,5 @@ struct TImg {
   }
 };
 
-// Block masks of a wave's 4 x 4 grid of 16 x 16 blocks (bit 4 x + y): the
-// first nv block rows (x < nv) or block columns (y < nv).
-__host__ __device__ inline unsigned rows_mask(int nv) { return nv >= 4 ? 0xFFFFu : ((1u << (4 * nv)) - 1u); }
-__host__ __device__ inline unsigned cols_mask(int nv) {
-  const unsigned c = nv >= 4 ? 0xFu : ((1u << nv) - 1u);
-  return c | (c << 4) | (c << 8) | (c << 12);
-}
-
 }  // namespace tdma
 }  // namespace tk
