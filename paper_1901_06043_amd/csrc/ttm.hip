@@ -576,9 +576,140 @@ __global__ __launch_bounds__(64 * kResWaves) void ttm_resident_kernel(const TI* 
   }
 }
 
+// Small product on slabs (L even, J <= 32, K <= 64): bound by reading Y and
+// writing Z, with a few MFMA steps per column.  A lane owns two neighbouring
+// columns of each row, so that a row of a wave's tile is one 128- or 256-byte
+// piece on both sides, both MFMA column groups share each factor operand, and
+// the next tile's loads are in flight during the products and stores of the
+// current one (two register sets, the loop unrolled by two so that no set is
+// moved).  MFMA step s of block jb takes reduction rows 16 jb + 4 s + q; steps
+// of padding rows only are left out.  Stores are nontemporal (9% less time on
+// the 36.9 GB output below, no loss on outputs that are read again at once).
+// The resident kernel below takes one 16-column group per wave, loads it and
+// waits: 12 -> 50 rows of 256x256x256x11x12, 36.9 GB of float output, took
+// 22.7 ms from doubles (FP64 products) and 20.0 ms from floats (FP32), and
+// takes 11.0 ms (5.0 TB/s) and 11.5 ms here.  Four columns per lane for
+// floats measured the same.
+template <typename TI, typename TO, typename CT, int RB, int NJ>
+__global__ __launch_bounds__(256, 2) void ttm_slab_kernel(const TI* __restrict__ Y, int J, uint32_t L, uint32_t cols,
+                                                          const double* __restrict__ M, int64_t msk, int64_t msj,
+                                                          int K, TO* __restrict__ Z, int64_t nct) {
+  using A = Acc<CT>;
+  using ML = MLds<CT>;
+  constexpr int V = 2;
+  typedef TI ivec __attribute__((ext_vector_type(V)));
+  typedef TO ovec __attribute__((ext_vector_type(V)));
+  constexpr int JP = 16 * NJ, LDM = sizeof(CT) == 4 ? 68 : 34;  // (MLds::ld(JP))
+  static_assert(NJ <= 2, "J <= 32");
+  __shared__ __align__(16) CT sM[16 * RB * LDM];  // row k: position 16 jb + 4 q + s holds index 16 jb + 4 s + q
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int e = tid; e < 16 * RB * JP; e += 256) {
+    const int k = e / JP, p = e - k * JP;
+    const int j = (p & ~15) | ((p & 3) << 2) | ((p >> 2) & 3);
+    sM[k * LDM + p] = (k < K && j < J) ? (CT)M[(int64_t)k * msk + (int64_t)j * msj] : (CT)0;
+  }
+  __syncthreads();
+  const int q = lane >> 4, i = lane & 15;
+  const int64_t JL = (int64_t)J * L;
+  const int64_t stride = (int64_t)gridDim.x * 4;
+  int64_t ct = (int64_t)blockIdx.x * 4 + wave;
+  // the lane's first column of tile t (cols and L are multiples of V)
+  auto first = [&](int64_t t) __attribute__((always_inline)) { return t * (16 * V) + V * i; };
+  auto load = [&](int64_t t, ivec (&r)[NJ][4]) __attribute__((always_inline)) {
+    const uint32_t c = (uint32_t)min(first(t), (int64_t)cols - V);
+    const uint32_t m = c / L, l = c - m * L;
+    const TI* src = Y + ((int64_t)l + JL * m);
+#pragma unroll
+    for (int jb = 0; jb < NJ; ++jb)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        r[jb][s] = *reinterpret_cast<const ivec*>(src + (int64_t)L * min(16 * jb + 4 * s + q, J - 1));
+  };
+  auto tile = [&](int64_t t, const ivec (&r)[NJ][4]) __attribute__((always_inline)) {
+    // rows past J hold a repeated row: its factor entries are zero, and the
+    // values are cleared too (an infinity times zero is not zero)
+    CT y[NJ][4][V];
+#pragma unroll
+    for (int jb = 0; jb < NJ; ++jb)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int v = 0; v < V; ++v) y[jb][s][v] = (16 * jb + 4 * s + q < J) ? (CT)r[jb][s][v] : (CT)0;
+    const int64_t c = first(t);
+    const bool cok = c < (int64_t)cols;
+    const uint32_t m = (uint32_t)c / L, l = (uint32_t)c - m * L;
+    TO* dst = Z + ((int64_t)l + (int64_t)L * K * m);
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      typename A::type acc[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) acc[v] = typename A::type{0, 0, 0, 0};
+#pragma unroll
+      for (int jb = 0; jb < NJ; ++jb) {
+        CT a4[4];
+        ML::read4(&sM[(16 * b + i) * LDM + 16 * jb + 4 * q], a4);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          if (16 * jb + 4 * s >= J) break;  // uniform
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[v] = A::mfma(a4[s], y[jb][s][v], acc[v]);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int k = 16 * b + A::row(q, v);
+        ovec o;
+#pragma unroll
+        for (int u = 0; u < V; ++u) o[u] = static_cast<TO>(acc[u][v]);
+        if (cok && k < K) __builtin_nontemporal_store(o, reinterpret_cast<ovec*>(dst + (int64_t)L * k));
+      }
+    }
+  };
+  ivec r0[NJ][4], r1[NJ][4];
+  if (ct < nct) load(ct, r0);
+  while (ct < nct) {
+    if (ct + stride < nct) load(ct + stride, r1);
+    tile(ct, r0);
+    ct += stride;
+    if (ct >= nct) break;
+    if (ct + stride < nct) load(ct + stride, r0);
+    tile(ct, r1);
+    ct += stride;
+  }
+}
+
+template <typename TI, typename TO, typename CT>
+void launch_ttm_slab(const TI* Y, int J, uint64_t L, uint64_t cols, const double* M, int64_t msk, int64_t msj, int K,
+                     TO* Z, hipStream_t stream) {
+  const int64_t nct = ceil_div((int64_t)cols, 32);
+  const int64_t grid = std::min<int64_t>(ceil_div(nct, 4), 256 * 4);
+  const int rb = (int)ceil_div(K, 16);
+#define TS_LAUNCH(RBV, NJV)                                                                                    \
+  hipLaunchKernelGGL((ttm_slab_kernel<TI, TO, CT, RBV, NJV>), dim3(grid), dim3(256), 0, stream, Y, J,       \
+                     (uint32_t)L, (uint32_t)cols, M, msk, msj, K, Z, nct)
+#define TS_NJ(RBV)                       \
+  do {                                   \
+    if (J <= 16) TS_LAUNCH(RBV, 1);      \
+    else TS_LAUNCH(RBV, 2);              \
+  } while (0)
+  if (rb == 1) TS_NJ(1);
+  else if (rb == 2) TS_NJ(2);
+  else if (rb == 3) TS_NJ(3);
+  else TS_NJ(4);
+#undef TS_NJ
+#undef TS_LAUNCH
+}
+
 template <typename TI, typename TO, typename CT>
 hipError_t launch_ttm_ct(const TI* Y, int J, uint64_t L, uint64_t cols, const double* M, int64_t msk, int64_t msj,
                          int K, TO* Z, hipStream_t stream) {
+  // pairs of columns on both sides; past 32 rows the resident kernel's loads
+  // of several blocks are in flight anyway (33 -> 33 rows: 5.1 TB/s)
+  if (L > 1 && L % 2 == 0 && J <= 32 && K <= 64 && reinterpret_cast<uintptr_t>(Y) % (2 * sizeof(TI)) == 0 &&
+      reinterpret_cast<uintptr_t>(Z) % (2 * sizeof(TO)) == 0) {
+    launch_ttm_slab<TI, TO, CT>(Y, J, L, cols, M, msk, msj, K, Z, stream);
+    return hipGetLastError();
+  }
   const int rbr = (int)ceil_div(K, 16);
   const size_t lds = sizeof(CT) * (size_t)(16 * rbr) * (size_t)MLds<CT>::ld((int)(16 * ceil_div(J, 16)));
   if (K <= 64 && lds <= (size_t)kResidentLds) {

@@ -3,7 +3,8 @@ kernel takes, itself or through an aligned copy of the factor, against numpy
 in FP64.
 
 Tolerance: a sum of J products in another order differs by at most about
-J u |M||Y| (1e-12 of it here), plus one rounding of a float32 output.
+J u |M||Y| (1e-12 of it here), plus one rounding of a float32 output; FP32
+products (J + 2) 2^-23 |M||Y|.
 """
 import numpy as np
 import pytest
@@ -21,7 +22,7 @@ def tk():
     return tk
 
 
-def check(tk, dims, n, K, layout, ydt, zdt, offset=0):
+def check(tk, dims, n, K, layout, ydt, zdt, offset=0, fp32=False):
     rng = np.random.default_rng(sum(dims) + K)
     shape = list(reversed(dims))
     Y = rng.standard_normal(shape).astype(ydt)
@@ -37,12 +38,14 @@ def check(tk, dims, n, K, layout, ydt, zdt, offset=0):
         wide = torch.zeros((K, 2 * dims[n]), dtype=torch.float64, device="cuda")
         wide[:, ::2] = torch.from_numpy(M)
         m = wide[:, ::2]
-    z = tk.ttm(buf[offset:].view(shape), n, m, dims=dims, out_dtype=t[zdt]).cpu().numpy()
+    z = tk.ttm(buf[offset:].view(shape), n, m, dims=dims, out_dtype=t[zdt], fp32_products=fp32).cpu().numpy()
     ax = len(dims) - 1 - n
     ref = np.moveaxis(np.tensordot(M, Y.astype(np.float64), axes=([1], [ax])), 0, ax)
     mag = np.moveaxis(np.tensordot(np.abs(M), np.abs(Y).astype(np.float64), axes=([1], [ax])), 0, ax)
     assert z.dtype == zdt
     tol = 1e-12 * mag + (2.0 ** -23 * np.abs(ref) if zdt == np.float32 else 0.0)
+    if fp32:
+        tol = tol + (dims[n] + 2) * 2.0 ** -23 * mag
     assert np.all(np.abs(z - ref) <= tol), (dims, n, K, layout)
 
 
@@ -104,3 +107,29 @@ def test_odd_factors_whole_path(tk, orc, dims, ranks):
             got = t.reconstruct(b, e, out_dtype=dt).cpu().numpy().reshape(-1)
             assert np.abs(got - part).max() <= tol * np.abs(part).max()
         t.free()
+
+
+# small products on slabs of pairs of columns: one and two blocks of reduction
+# rows (whole, ragged, one row), one to four blocks of output rows, fewer
+# columns than a wave's tile, a column count that ends inside one, several
+# tiles per wave; odd slabs and unaligned bases take the other kernel
+@pytest.mark.parametrize("dims,n,K", [
+    ([2, 1, 3], 1, 1), ([2, 16, 5], 1, 16), ([6, 17, 40], 1, 17), ([34, 12, 3], 1, 50), ([64, 32], 1, 64),
+    ([30, 5, 11, 7], 2, 33), ([1000, 31, 3], 1, 48), ([3, 12, 20], 1, 50), ([700, 4, 400], 1, 10),
+])
+def test_ttm_small_slabs(tk, dims, n, K):
+    for ydt in (np.float64, np.float32):
+        for zdt in (np.float64, np.float32):
+            for fp32 in (False, True):
+                check(tk, dims, n, K, "columns", ydt, zdt, fp32=fp32)
+            check(tk, dims, n, K, "rows", ydt, zdt, offset=1)
+
+
+def test_ttm_small_slabs_infinity(tk):
+    """A row past J is not multiplied in: an infinity stays in its own column."""
+    y = torch.zeros((3, 5, 8), dtype=torch.float64, device="cuda")
+    y[1, 4, 3] = float("inf")
+    z = tk.ttm(y, 1, torch.ones((7, 5), dtype=torch.float64, device="cuda"))
+    want = torch.zeros((3, 7, 8), dtype=torch.float64)
+    want[1, :, 3] = float("inf")
+    assert torch.equal(z.cpu(), want)
