@@ -7,30 +7,38 @@
 // over a 32-column chunk and in FP64 across chunks.
 //
 // Work items: a pair of 128-row tiles (ta <= tb) and a contiguous range of
-// column chunks.  Four waves per workgroup; each holds a 64 x 64 part of the
-// pair's 128 x 128 output as 4 x 4 blocks of 16 x 16 in FP64 MFMA
-// accumulators (v_mfma_f64_16x16x4f64), so a step of four columns reads 8
-// operands from LDS for 16 MFMAs.  Diagonal pairs compute the upper triangle
-// only (gram_dma.hpp: wave_task), and blocks of rows at or beyond J are
-// skipped, so a ragged last tile costs only its rows.  About 8192 items: the
-// faster diagonal and ragged items then even out over the run (with two items
-// per workgroup slot the run ended on a long tail of slow items).
+// column chunks.  Eight waves per workgroup; wave w multiplies the 16 rows of
+// block w of tile ta with up to eight blocks of tile tb (all of them for an
+// off-diagonal pair; four or five for a diagonal one, chosen so that the
+// waves share its 36 blocks evenly: gram_dma.hpp), in FP64 MFMA accumulators.
+// 128 registers per lane leave four waves per SIMD from two workgroups, which
+// cover each other's operand reads, load issue and barriers.  Four waves of
+// 64 x 64 (two per SIMD) covered them less, and the reduced forms, which keep
+// FP32 sums or bf16 pieces beside the FP64 accumulators, fitted only one such
+// workgroup on a CU; with one block column at a time they now fit two.
+// J^2 K flops over the time, before and after: FP64 672x448x33x64 doubles,
+// mode 0: 46.7 -> 58 TF, mode 1 of 448x672x33x64: 45.6 -> 55 TF (FP64 MFMA
+// bound, with 4 TB/s of tile reads beyond L2 close behind); FP32 mode 0 of
+// 672x448x33x64: 52 -> 73 TF; 161x161x160x11x25 (unaligned columns, on the
+// register-staged kernel before): FP32 20.6 -> 49, BF16X6 15.9 -> 46 TF.
+// Blocks of rows at or beyond J are skipped, so a ragged last tile costs only
+// its rows.  About 8192 items: the faster diagonal and ragged items then even
+// out over the run (with two items per workgroup slot the run ended on a long
+// tail of slow items).
 //
 // Staging: the chunk images (gram_dma.hpp) are written straight from global
-// memory into LDS (global_load_lds, 64 lanes x 16 bytes per instruction),
-// with no registers in between; tensors whose rows or columns are not
-// 16-byte aligned use the tile-pair kernels of gram_mixed.hip instead.
-// Elements outside the tensor are not loaded: rows >= J feed only rows and
-// columns of S that are dropped, and the columns past the end of the
-// unfolding (or of a slab of L columns) are zeroed in LDS.  Each workgroup
-// double-buffers its chunks (64 or 80 KB), so two workgroups fit on a CU and
-// one's barriers overlap the other's MFMAs; the loads of the next chunk run
-// during the MFMAs of the current one (chunk_loop).
+// memory into LDS (global_load_lds, 64 lanes x 16 bytes per instruction, or 4
+// bytes where the rows or columns are not 16-byte aligned), with no registers
+// in between, from pointers advanced by a fixed stride per chunk.  Rows >= J
+// feed only rows and columns of S that are dropped, and the columns past the
+// end of the unfolding (or of a slab of L columns) are zeroed in LDS.  Each
+// workgroup double-buffers its chunks (64 or 80 KB); the loads of the next
+// chunk run during the MFMAs of the current one (chunk_loop).
 //
 // Output: every item writes its FP64 partial blocks in the layout of the
 // tile-pair reduction (gram_mixed.hip), which sums the splits in a fixed
 // order.  ||Y||^2 is the trace of S with FP64 products (its diagonal entries
-// are FP64 sums of squares of the values as loaded); with FP32 products the
+// are FP64 sums of squares of the values as loaded); with reduced products the
 // diagonal items sum the squares of their tile's rows in FP64 from LDS.
 #include "common.hpp"
 #include "gram_dma.hpp"
@@ -42,7 +50,7 @@ namespace {
 
 using dma::Img;
 
-constexpr int kDW = 4;           // waves per workgroup
+constexpr int kDW = 8;           // waves per workgroup
 constexpr int kDNT = 64 * kDW;   // threads per workgroup
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -70,147 +78,126 @@ __device__ __forceinline__ void decode_pair_dma(int p, int ntiles, int& ta, int&
   tb = t + p;
 }
 
-// First column and valid column count of chunk ch (layout 1: and the slab's
-// element offset).
-template <typename T, int LAY>
-__device__ __forceinline__ void chunk_cols(const DmaParams& g, int64_t ch, int64_t& c0, int& ncol, int64_t& base_m) {
-  using I = Img<sizeof(T), LAY>;
-  if constexpr (LAY == 0) {
-    c0 = ch * I::KC;
-    ncol = (int)min((int64_t)I::KC, g.K - c0);
-    base_m = 0;
-  } else {
-    const int64_t m = ch / g.CL;
-    c0 = (ch - m * g.CL) * I::KC;
-    ncol = (int)min((int64_t)I::KC, g.L - c0);
-    base_m = m * g.L * g.J;
-  }
+template <int W>
+__device__ __forceinline__ void load_lds(const char* src, char* dst) {
+  if constexpr (W == 16) __builtin_amdgcn_global_load_lds(static_cast<const void*>(src), (lds_void*)dst, 16, 0, 0);
+  else __builtin_amdgcn_global_load_lds(static_cast<const void*>(src), (lds_void*)dst, 4, 0, 0);
 }
 
-// Issues the loads of chunk ch into one buffer.  Instruction j of the chunk
-// covers bytes [1024 jj, 1024 (jj + 1)) of tile image p (jj = j mod IPS);
-// wave w issues j = w, w + 4, ...  Lanes whose element lies outside the
-// tensor issue nothing: rows >= J only feed rows and columns of S that are
-// not kept, and columns past the chunk's end are zeroed by fill_chunk.
-// Addresses are split into a part common to the wave (scalar) and a small
-// per-lane part, so that an instruction costs a few vector operations.
-template <typename T, int LAY>
-__device__ __forceinline__ void issue_chunk(const DmaParams& g, int64_t ch, char* buf, int nslots, int r0a, int r0b,
-                                            int wave, int lane) {
+// Per-lane state of an item's loads: one pointer per tile image.  Instruction
+// jj of an image covers its bytes [64 W jj, 64 W (jj + 1)), W bytes per lane;
+// a wave issues every eighth one, and the swizzles repeat over those, so that
+// they differ by a distance common to the wave (whole columns in layout 0,
+// rows in layout 1).  Layout 0: rows >= J are clamped into the tensor; layout
+// 1: they are left out.
+template <typename T, int LAY, int W>
+struct Loader {
   using I = Img<sizeof(T), LAY>;
-  constexpr int ES = sizeof(T), W = 16;
-  constexpr int IPS = I::TB / (64 * W);
-  int64_t c0, base_m;
-  int ncol;
-  chunk_cols<T, LAY>(g, ch, c0, ncol, base_m);
-  const int n = nslots * IPS;
-  if constexpr (LAY == 1) {
-    // instruction jj: rows RPI jj .. RPI jj + RPI - 1 of the tile, LPR lanes per row
-    constexpr int LPR = 128 / W, RPI = 64 / LPR;
-    const int rl = lane / LPR, wb = (lane % LPR) * W;
-    const int64_t lane_row = (int64_t)rl * g.L * ES;  // bytes to the lane's row
-    for (int j = wave; j < n; j += kDW) {
-      const int p = (j >= IPS) ? 1 : 0;
-      const int jj = j - p * IPS;
-      const int rt = (p ? r0b : r0a) + RPI * jj;  // the instruction's first row in the tensor
-      const int r = RPI * jj + rl;                // the lane's row in the tile
-      const int u = (wb >> 4) ^ ((r >> 1) & 7);
-      const int c = u * I::E + (wb & 15) / ES;
-      if (rt + rl < g.J && c < ncol) {
-        const int64_t wave_off = ((c0 + base_m) + g.L * (int64_t)rt) * ES;
-        const void* src = static_cast<const void*>(g.Y + wave_off + lane_row + (c * ES + (wb & 15) % ES));
-        char* dst = buf + p * I::TB + jj * 64 * W;
-        __builtin_amdgcn_global_load_lds(src, (lds_void*)dst, 16, 0, 0);
-      }
+  static constexpr int ES = sizeof(T);
+  static constexpr int IPS = I::TB / (64 * W);         // instructions per tile image
+  static constexpr int NI = (IPS + kDW - 1) / kDW;     // per wave and image
+  static constexpr int RS = kDW * 64 * W / 128;        // layout 1: rows between a wave's instructions
+  const char* p[2];
+  int64_t step;   // bytes between a wave's instructions of one image
+  int rows[2];    // layout 1: rows from the lane's first row to J, per image
+  bool whole;     // layout 1: all rows of both tiles lie in the tensor
+  int64_t cc;     // layout 1: chunk within its slab
+  int64_t left;   // layout 0: columns from the next chunk's first to K
+  int ncol;       // valid columns of the chunk to be loaded next
+
+  // the wave's first instruction of image s (20 per image: 4 waves issue 3 of
+  // the first image and 2 of the second, the others 2 and 3)
+  __device__ __forceinline__ static int first(int s, int wave) { return (s && IPS % kDW) ? (wave ^ 4) : wave; }
+
+  __device__ __forceinline__ void init(const DmaParams& g, int64_t ch, int r0a, int r0b, int wave, int lane) {
+    int64_t base;  // element offset of the chunk's first column
+    if constexpr (LAY == 0) {
+      base = ch * I::KC * g.J;
+      left = g.K - ch * I::KC;
+      ncol = (int)min((int64_t)I::KC, left);
+      step = (int64_t)(kDW * 64 * W / I::CB) * g.J * ES;
+    } else {
+      const int64_t m = ch / g.CL;
+      cc = ch - m * g.CL;
+      base = m * g.L * g.J + cc * I::KC;
+      ncol = (int)min((int64_t)I::KC, g.L - cc * I::KC);
+      step = (int64_t)RS * g.L * ES;
+      whole = max(r0a, r0b) + dma::kTileRows <= g.J;
     }
-  } else {
-    for (int j = wave; j < n; j += kDW) {
-      const int p = (j >= IPS) ? 1 : 0;
-      const int jj = j - p * IPS;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
       int r, c, b;
-      I::inv(jj * 64 * W + lane * W, r, c, b);
-      const int rt = p ? r0b : r0a;
-      if (rt + r < g.J && c < ncol) {
-        const int64_t wave_off = ((int64_t)rt + (int64_t)g.J * c0) * ES;
-        const void* src = static_cast<const void*>(g.Y + wave_off + ((r + g.J * c) * ES + b));
-        char* dst = buf + p * I::TB + jj * 64 * W;
-        __builtin_amdgcn_global_load_lds(src, (lds_void*)dst, 16, 0, 0);
+      I::inv(first(s, wave) * (64 * W) + lane * W, r, c, b);
+      const int r0 = s ? r0b : r0a;
+      // (layout 0: a unit holds E rows, and J is a multiple of E where W = 16)
+      const int row = min(r0 + r, (LAY == 0 && W == 16) ? g.J - I::E : g.J - 1);
+      p[s] = g.Y + (base + ((LAY == 0) ? (int64_t)row + (int64_t)g.J * c : (int64_t)row * g.L + c)) * ES + b;
+      rows[s] = g.J - r0 - r;
+    }
+  }
+
+  // The column of the chunk that this lane's part of instruction jj holds.
+  __device__ __forceinline__ static int column(int jj, int lane) {
+    int r, c, b;
+    I::inv(jj * (64 * W) + lane * W, r, c, b);
+    return c;
+  }
+
+  // TEST: columns past the chunk's end and rows past J are left out.
+  template <bool TEST>
+  __device__ __forceinline__ void issue_all(char* buf, int nslots, int wave, int lane) const {
+    if constexpr (TEST) asm volatile("" : "+v"(lane));
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      if (s >= nslots) break;  // uniform
+#pragma unroll
+      for (int k = 0; k < NI; ++k) {
+        const int jj = first(s, wave) + kDW * k;
+        if (jj >= IPS) break;  // uniform
+        if (!TEST || ((LAY == 0 || RS * k < rows[s]) && column(jj, lane) < ncol))
+          load_lds<W>(p[s] + k * step, buf + s * I::TB + jj * (64 * W));
       }
     }
   }
-}
-
-// Zeros the positions of chunk ch's columns past its end (the last chunk of
-// the unfolding, or of a slab of L columns when KC does not divide L).  Called
-// once the wave's own loads have landed, so that no load is in flight; no
-// load ever targets these positions.
-template <typename T, int LAY>
-__device__ __forceinline__ void fill_chunk(const DmaParams& g, int64_t ch, char* buf, int nslots, int wave,
-                                           int lane) {
-  using I = Img<sizeof(T), LAY>;
-  constexpr int W = 16;
-  constexpr int IPS = I::TB / (64 * W);
-  int64_t c0, base_m;
-  int ncol;
-  chunk_cols<T, LAY>(g, ch, c0, ncol, base_m);
-  if (ncol >= I::KC) return;
-  const int n = nslots * IPS;
-  for (int j = wave; j < n; j += kDW) {
-    const int p = (j >= IPS) ? 1 : 0;
-    const int jj = j - p * IPS;
-    int r, c, b;
-    I::inv(jj * 64 * W + lane * W, r, c, b);
-    if (c >= ncol) {
-      char* dst = buf + p * I::TB + jj * 64 * W + lane * W;
-      *reinterpret_cast<uint4*>(dst) = uint4{0u, 0u, 0u, 0u};
+  // Loads the next chunk into buf.
+  __device__ __forceinline__ void issue(char* buf, int nslots, int wave, int lane) const {
+    if (ncol >= I::KC && (LAY == 0 || whole)) issue_all<false>(buf, nslots, wave, lane);
+    else issue_all<true>(buf, nslots, wave, lane);
+  }
+  // Zeros the positions of that chunk's columns past its end (the last chunk of
+  // the unfolding, or of a slab of L columns when KC does not divide L), then
+  // moves on.  Called once the wave's own loads have landed; no load ever
+  // targets these positions.
+  __device__ __forceinline__ void finish(const DmaParams& g, char* buf, int nslots, int wave, int lane) {
+    if (ncol < I::KC) {
+      asm volatile("" : "+v"(lane));
+#pragma unroll 1
+      for (int s = 0; s < nslots; ++s)
+#pragma unroll 1
+        for (int jj = first(s, wave); jj < IPS; jj += kDW)
+          if (column(jj, lane) >= ncol) {
+            char* at = buf + s * I::TB + jj * (64 * W) + lane * W;
+            if constexpr (W == 16) *reinterpret_cast<uint4*>(at) = uint4{0u, 0u, 0u, 0u};
+            else *reinterpret_cast<uint32_t*>(at) = 0u;
+          }
     }
+    int64_t d;  // bytes to the next chunk
+    if constexpr (LAY == 0) {
+      d = (int64_t)I::KC * g.J * ES;
+      left -= I::KC;
+      ncol = (int)min((int64_t)I::KC, left);
+    } else {
+      d = I::KC * ES;
+      if (++cc == g.CL) {
+        cc = 0;
+        d = (g.L * g.J - (g.CL - 1) * I::KC) * ES;
+      }
+      ncol = (int)min((int64_t)I::KC, g.L - cc * I::KC);
+    }
+    p[0] += d;
+    p[1] += d;
   }
-}
-
-template <typename T, int LAY>
-struct Ops;
-
-// layout 0: one element per operand and step
-template <typename T>
-struct Ops<T, 0> {
-  using I = Img<sizeof(T), 0>;
-  static constexpr int NG = I::KC / 4;  // operand groups (steps) per chunk
-  static constexpr int GS = 1;          // steps per group
-  T a[4], b[4];
-  int d;  // unused
-  __device__ __forceinline__ void read(const char* buf, const int (&oa)[4], const int (&ob)[4], int g) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) a[t] = *reinterpret_cast<const T*>(buf + oa[t] + g * 4 * I::CB);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) b[t] = *reinterpret_cast<const T*>(buf + ob[t] + g * 4 * I::CB);
-  }
-  __device__ __forceinline__ T A(int t, int) const { return a[t]; }
-  __device__ __forceinline__ T B(int t, int) const { return b[t]; }
 };
-
-// layout 1: one 16-byte unit per operand and group of E steps
-template <typename T>
-struct Ops<T, 1> {
-  using I = Img<sizeof(T), 1>;
-  static constexpr int NG = 2;
-  static constexpr int GS = I::E;
-  typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));
-  V a[4], b[4];
-  int d;  // byte distance from unit q to unit q | 4 of the lane's rows
-  __device__ __forceinline__ void read(const char* buf, const int (&oa)[4], const int (&ob)[4], int g) {
-    const int o = g ? d : 0;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) a[t] = *reinterpret_cast<const V*>(buf + oa[t] + o);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) b[t] = *reinterpret_cast<const V*>(buf + ob[t] + o);
-  }
-  __device__ __forceinline__ T A(int t, int s) const { return a[t][s]; }
-  __device__ __forceinline__ T B(int t, int s) const { return b[t][s]; }
-};
-
-// MK: the compile-time block mask (gram_dma.hpp), or kGeneric for a mask
-// known only at run time (ragged last tiles), tested block by block.
-constexpr unsigned kGeneric = 0x10000u;
 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
@@ -229,10 +216,15 @@ __device__ __forceinline__ void split8(const float (&v)[8], bf8 (&p)[3]) {
   }
 }
 
-// The eight FP32 values of one operand block that lane (i, q) supplies to a
-// bf16 MFMA (K = 32, 8 per lane group): slot e holds the column that the FP32
-// form reads at its step e (Img::col(e, q)); off is the block's group-0 byte
-// offset, d (layout 1) the distance to the lane's second unit.
+// Operand offsets of a lane: row i of block 0 of a tile image, column 0 of
+// its lane group (Img::col); d (layout 1): the distance to its second unit.
+template <int ES, int LAY>
+__device__ __forceinline__ int blk_off(int o, int b) {
+  return LAY == 0 ? (o ^ (b * 16 * ES)) : o + b * 16 * 128;
+}
+
+// The eight FP32 values of one operand block that lane (i, q) supplies to the
+// chunk's products: slot e holds column Img::col(e, q).
 template <int LAY>
 __device__ __forceinline__ void read8(const char* buf, int off, int d, float (&v)[8]) {
   if constexpr (LAY == 0) {
@@ -246,101 +238,85 @@ __device__ __forceinline__ void read8(const char* buf, int off, int d, float (&v
   }
 }
 
-// BF16X6 products of one chunk (PREC 3).  The slot map of read8 is the same
-// for both operands, so slot e of lane group q is the same column in A and B.
-// The A blocks are split once per chunk, the B blocks one at a time; each
-// block's FP32 chunk sum, smallest terms first, is then added to its FP64
-// accumulator.
-template <unsigned MK, int LAY>
-__device__ __forceinline__ void compute_chunk_bf(const char* buf, const int (&oa)[4], const int (&ob)[4], int d,
-                                                 d4 (&acc)[4][4], unsigned mask) {
-  auto on = [&](int x, int y) {
-    return (MK == kGeneric) ? ((mask >> (4 * x + y)) & 1u) : ((MK >> (4 * x + y)) & 1u);
-  };
-  bf8 ap[4][3];
-#pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    float v[8];
-    read8<LAY>(buf, oa[x], d, v);
-    split8(v, ap[x]);
-  }
-#pragma unroll
-  for (int y = 0; y < 4; ++y) {
-    float v[8];
-    read8<LAY>(buf, ob[y], d, v);
-    bf8 bp[3];
-    split8(v, bp);
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      if (on(x, y)) {
-        f4 c = f4{0.f, 0.f, 0.f, 0.f};
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[x][2], bp[0], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[x][0], bp[2], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[x][1], bp[1], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[x][1], bp[0], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[x][0], bp[1], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[x][0], bp[0], c, 0, 0, 0);
-#pragma unroll
-        for (int v2 = 0; v2 < 4; ++v2) acc[x][y][v2] += (double)c[v2];
-      }
-    }
-  }
-}
+// MK: the compile-time block mask (gram_dma.hpp), or kGeneric for a mask
+// known only at run time (ragged last tiles), tested block by block.
+constexpr unsigned kGeneric = 0x100u;
 
-// PREC 0: FP64 products and accumulation.  PREC 1 (float input): FP32 MFMA
-// products accumulated in FP32 over the chunk's 32 columns, then added to
-// the FP64 accumulators.
+// The products of one chunk: A block `oa` (already the wave's) with the B
+// blocks of the slots in the mask; slot y's block is b0 + y (mod 8).
+// PREC 0: FP64 products and accumulation, step by step over all slots.
+// PREC 1 (FP32 MFMA) and 3 (BF16X6), float input: slot by slot, each slot's
+// products summed in FP32 over the chunk's 32 columns (BF16X6: smallest terms
+// first), then added to its FP64 accumulator.
 template <unsigned MK, typename T, int LAY, int PREC>
-__device__ __forceinline__ void compute_chunk(const char* buf, const int (&oa)[4], const int (&ob)[4], int d,
-                                              d4 (&acc)[4][4], unsigned mask) {
-  if constexpr (PREC == 3) {
-    compute_chunk_bf<MK, LAY>(buf, oa, ob, d, acc, mask);
-    return;
-  }
-  using O = Ops<T, LAY>;
-  O cur, nxt;
-  cur.d = nxt.d = d;
-  f4 acc32[4][4];
-  if constexpr (PREC == 1) {
+__device__ __forceinline__ void compute_chunk(const char* abuf, const char* bbuf, int oa, int ob, int d, int b0,
+                                              d4 (&acc)[8], unsigned mask) {
+  using I = Img<sizeof(T), LAY>;
+  constexpr int ES = sizeof(T);
+  // (derived offsets are formed again for each chunk rather than held in
+  // registers for both buffers, which spilled)
+  asm volatile("" : "+v"(oa), "+v"(ob), "+v"(d));
+  auto on = [&](int y) __attribute__((always_inline)) {
+    return (MK == kGeneric) ? ((mask >> y) & 1u) : ((MK >> y) & 1u);
+  };
+  auto boff = [&](int y) __attribute__((always_inline)) { return blk_off<ES, LAY>(ob, (b0 + y) & 7); };
+  if constexpr (PREC == 0 && LAY == 0) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int s = 0; s < I::KC / 4; ++s) {
+      __builtin_amdgcn_sched_barrier(0);  // one step's operands at a time
+      const double a = (double)*reinterpret_cast<const T*>(abuf + oa + s * 4 * I::CB);
+      T b[8];
 #pragma unroll
-      for (int y = 0; y < 4; ++y) acc32[x][y] = f4{0.f, 0.f, 0.f, 0.f};
-  }
-  cur.read(buf, oa, ob, 0);
+      for (int y = 0; y < 8; ++y)
+        if (on(y)) b[y] = *reinterpret_cast<const T*>(bbuf + boff(y) + s * 4 * I::CB);
 #pragma unroll
-  for (int g = 0; g < O::NG; ++g) {
-    if (g + 1 < O::NG) nxt.read(buf, oa, ob, g + 1);
-#pragma unroll
-    for (int s = 0; s < O::GS; ++s) {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-          const bool on = (MK == kGeneric) ? ((mask >> (4 * x + y)) & 1u) : ((MK >> (4 * x + y)) & 1u);
-          if (on) {
-            if constexpr (PREC == 0)
-              acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)cur.A(x, s), (double)cur.B(y, s), acc[x][y],
-                                                               0, 0, 0);
-            else
-              acc32[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.A(x, s), cur.B(y, s), acc32[x][y], 0, 0, 0);
-          }
-        }
-      }
+      for (int y = 0; y < 8; ++y)
+        if (on(y)) acc[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)b[y], acc[y], 0, 0, 0);
     }
-    if (g + 1 < O::NG) cur = nxt;
-  }
-  if constexpr (PREC == 1) {
+  } else if constexpr (PREC == 0) {
+    typedef T V __attribute__((ext_vector_type(I::E)));
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int g = 0; g < 2; ++g) {
+      __builtin_amdgcn_sched_barrier(0);
+      const V a = *reinterpret_cast<const V*>(abuf + oa + (g ? d : 0));
+      V b[8];
 #pragma unroll
-      for (int y = 0; y < 4; ++y) {
-        const bool on = (MK == kGeneric) ? ((mask >> (4 * x + y)) & 1u) : ((MK >> (4 * x + y)) & 1u);
-        if (on) {
+      for (int y = 0; y < 8; ++y)
+        if (on(y)) b[y] = *reinterpret_cast<const V*>(bbuf + boff(y) + (g ? d : 0));
 #pragma unroll
-          for (int v = 0; v < 4; ++v) acc[x][y][v] += (double)acc32[x][y][v];
-        }
+      for (int s = 0; s < I::E; ++s)
+#pragma unroll
+        for (int y = 0; y < 8; ++y)
+          if (on(y)) acc[y] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s], (double)b[y][s], acc[y], 0, 0, 0);
+    }
+  } else {
+    float a[8];
+    read8<LAY>(abuf, oa, d, a);
+    bf8 ap[3];
+    if constexpr (PREC == 3) split8(a, ap);
+#pragma unroll
+    for (int y = 0; y < 8; ++y) {
+      if (!on(y)) continue;
+      __builtin_amdgcn_sched_barrier(0);  // one slot's operands at a time
+      float b[8];
+      read8<LAY>(bbuf, boff(y), d, b);
+      f4 c = f4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (PREC == 3) {
+        bf8 bp[3];
+        split8(b, bp);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[2], bp[0], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[0], bp[2], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[1], bp[1], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[1], bp[0], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[0], bp[1], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[0], bp[0], c, 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], c, 0, 0, 0);
       }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[y][v] += (double)c[v];
+    }
   }
 }
 
@@ -371,124 +347,121 @@ __device__ __forceinline__ double chunk_sq(const char* buf, int r0, int J, int t
 // they run during chunk t's MFMAs; then the wave waits for them, zeros any
 // columns past the chunk's end and meets the others at the next barrier,
 // after which the buffer of chunk t is free for chunk t + 2.
-template <unsigned MK, typename T, int LAY, int PREC>
-__device__ __forceinline__ void chunk_loop(const DmaParams& g, int64_t split, int64_t ns, int64_t niter, char* buf0, char* buf1,
-                                           int nslots, int r0a, int r0b, int wave, int lane, const int (&oa)[4],
-                                           const int (&ob)[4], int d, d4 (&acc)[4][4], unsigned mask, double& sq) {
+template <unsigned MK, typename T, int LAY, int PREC, int W>
+__device__ __forceinline__ void chunk_loop(const DmaParams& g, Loader<T, LAY, W>& ld, int64_t niter, char* buf0,
+                                           char* buf1, int nslots, int r0a, int wave, int lane, int oa, int ob, int d,
+                                           int b0, d4 (&acc)[8], unsigned mask, double& sq) {
   // reduced forms: diagonal items also sum the squares of their tile's rows
   const bool dsq = (PREC >= 1) && nslots == 1;
+  const int pb = (nslots - 1) * Img<sizeof(T), LAY>::TB;  // B operand's tile image
   const int tid = 64 * wave + lane;
   if (niter <= 0) return;
-  issue_chunk<T, LAY>(g, split, buf0, nslots, r0a, r0b, wave, lane);
+  ld.issue(buf0, nslots, wave, lane);
   __builtin_amdgcn_s_waitcnt(0);
-  fill_chunk<T, LAY>(g, split, buf0, nslots, wave, lane);
+  ld.finish(g, buf0, nslots, wave, lane);
   __syncthreads();
-  for (int64_t t = 0;; t += 2) {
-    if (t + 1 < niter) issue_chunk<T, LAY>(g, split + (t + 1) * ns, buf1, nslots, r0a, r0b, wave, lane);
+  // (one exit from the loop: with two, the accumulators were copied between
+  // register sets in every round)
+  auto step = [&](char* cur, char* nxt, bool more) __attribute__((always_inline)) {
+    if (more) ld.issue(nxt, nslots, wave, lane);  // uniform
     if constexpr (PREC >= 1)
-      if (dsq) sq += chunk_sq<LAY>(buf0, r0a, g.J, tid);
-    compute_chunk<MK, T, LAY, PREC>(buf0, oa, ob, d, acc, mask);
-    if (t + 1 >= niter) break;
-    __builtin_amdgcn_s_waitcnt(0);
-    fill_chunk<T, LAY>(g, split + (t + 1) * ns, buf1, nslots, wave, lane);
-    __syncthreads();
-    if (t + 2 < niter) issue_chunk<T, LAY>(g, split + (t + 2) * ns, buf0, nslots, r0a, r0b, wave, lane);
-    if constexpr (PREC >= 1)
-      if (dsq) sq += chunk_sq<LAY>(buf1, r0a, g.J, tid);
-    compute_chunk<MK, T, LAY, PREC>(buf1, oa, ob, d, acc, mask);
-    if (t + 2 >= niter) break;
-    __builtin_amdgcn_s_waitcnt(0);
-    fill_chunk<T, LAY>(g, split + (t + 2) * ns, buf0, nslots, wave, lane);
-    __syncthreads();
+      if (dsq) sq += chunk_sq<LAY>(cur, r0a, g.J, tid);
+    compute_chunk<MK, T, LAY, PREC>(cur, cur + pb, oa, ob, d, b0, acc, mask);
+    if (more) {
+      __builtin_amdgcn_s_waitcnt(0);
+      ld.finish(g, nxt, nslots, wave, lane);
+      __syncthreads();
+    }
+  };
+  int64_t t = 0;
+  for (; t + 1 < niter; t += 2) {
+    step(buf0, buf1, true);
+    step(buf1, buf0, t + 2 < niter);
   }
+  if (t < niter) step(buf0, buf1, false);
 }
 
-// FP64 products: two workgroups per CU (at most 256 registers per lane).
-// The reduced forms keep FP32 chunk sums or bf16 pieces beside the FP64
-// accumulators, which does not fit 256 registers: one workgroup (one wave per
-// SIMD) per CU.
-template <typename T, int LAY, int PREC>
-__global__ __launch_bounds__(kDNT, PREC == 0 ? 2 : 1) void gram_dma_kernel(DmaParams g) {
+// The whole item of one mask class: accumulators zeroed, all chunks, then the
+// partial blocks (one copy per class, so that no accumulator is merged across
+// classes).  MFMA result, lane l, register v: FP64 D[(l >> 4) + 4 v][l & 15],
+// FP32 D[4 (l >> 4) + v][l & 15].  A diagonal pair's block (w, b) with b < w
+// is the transpose of block (b, w).
+template <unsigned MK, typename T, int LAY, int PREC, int W>
+__device__ __forceinline__ double item_body(const DmaParams& g, Loader<T, LAY, W>& ld, int64_t niter, char* buf0,
+                                            char* buf1, bool diag, int r0a, int wave, int lane, int oa, int ob, int d,
+                                            unsigned mask, double* __restrict__ P) {
+  d4 acc[8];
+#pragma unroll
+  for (int y = 0; y < 8; ++y) acc[y] = d4{0.0, 0.0, 0.0, 0.0};
+  double sq = 0.0;
+  const int b0 = diag ? wave : 0;
+  chunk_loop<MK, T, LAY, PREC, W>(g, ld, niter, buf0, buf1, diag ? 1 : 2, r0a, wave, lane, oa, ob, d, b0, acc, mask,
+                                  sq);
+  const int i = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int y = 0; y < 8; ++y) {
+    if ((MK == kGeneric) ? ((mask >> y) & 1u) : ((MK >> y) & 1u)) {
+      const int b = (b0 + y) & 7;
+      const bool flip = diag && b < wave;
+      const int qb = diag ? dma::tri_index(min(b, wave), max(b, wave)) : wave * 8 + b;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = (PREC == 0) ? q + 4 * v : 4 * q + v;
+        P[(int64_t)qb * 256 + (flip ? i * 16 + r : r * 16 + i)] = acc[y][v];
+      }
+    }
+  }
+  return sq;
+}
+
+// BF16X6 with 16-byte loads runs one workgroup per CU: the pieces of two
+// operand blocks beside the accumulators spill at 128 registers (4.2 against
+// 3.6 ms for a 256x256x256x11x5 mode); with 4-byte loads, whose issue needs
+// covering, two workgroups are the faster (4.0 against 5.6 ms, 161x161x160x11x25).
+template <typename T, int LAY, int PREC, int W>
+__global__ __launch_bounds__(kDNT, PREC == 3 && W == 16 ? 2 : 4) void gram_dma_kernel(DmaParams g) {
   static_assert(PREC == 0 || sizeof(T) == 4, "the reduced forms read float input");
   using I = Img<sizeof(T), LAY>;
   __shared__ __attribute__((aligned(16))) char buf0[2 * I::TB];
   __shared__ __attribute__((aligned(16))) char buf1[2 * I::TB];
   const int64_t item = xcd_remap(blockIdx.x, gridDim.x, g.total);
   if (item < 0) return;
-  const int pair = (int)(item % g.npairs);
-  const int64_t split = item / g.npairs;
+  const int64_t split = (uint32_t)item / (uint32_t)g.npairs;  // total < 2^31
+  const int pair = (int)(item - split * g.npairs);
   int ta, tb;
   decode_pair_dma(pair, g.ntiles, ta, tb);
   const bool diag = (ta == tb);
-  const int nslots = diag ? 1 : 2;
   const int r0a = 128 * ta, r0b = 128 * tb;
   // split s takes the contiguous chunks [s cps, (s + 1) cps)
-  const int64_t c0 = split * g.cps, cstep = 1, niter = min(g.cps, g.nchunks - c0);
+  const int64_t ch0 = split * g.cps, niter = min(g.cps, g.nchunks - ch0);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, q = lane >> 4;
-  int a0, b0, bs;
-  unsigned mask;
-  dma::wave_task(wave, diag, r0a, r0b, g.J, a0, b0, bs, mask);
-  a0 = __builtin_amdgcn_readfirstlane(a0);
-  b0 = __builtin_amdgcn_readfirstlane(b0);
-  bs = __builtin_amdgcn_readfirstlane(bs);
-  mask = __builtin_amdgcn_readfirstlane(mask);
-  const int pb = diag ? 0 : I::TB;  // B operand's tile image
-
-  // operand byte offsets (group 0) of this lane's four A and four B blocks
-  int oa[4], ob[4], d = 0;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    oa[t] = I::at(16 * (a0 + t) + i, I::col(0, q));
-    ob[t] = pb + I::at(16 * (b0 + bs * t) + i, I::col(0, q));
-  }
-  if constexpr (LAY == 1) d = I::at(i, I::col(I::E, q)) - I::at(i, I::col(0, q));
-
-  d4 acc[4][4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) acc[x][y] = d4{0.0, 0.0, 0.0, 0.0};
-
-  // one copy of the loop per mask class, so that the accumulators flow
-  // through a single chain of MFMAs; waves without blocks still load and
-  // meet the barriers
+  const unsigned mask = __builtin_amdgcn_readfirstlane(dma::wave_mask(wave, diag, r0a, r0b, g.J));
+  const int o0 = I::at(i, I::col(0, q));
+  const int oa = blk_off<sizeof(T), LAY>(o0, wave);
+  const int d = (LAY == 1) ? I::at(i, I::col(I::E, q)) - o0 : 0;
+  Loader<T, LAY, W> ld;
+  ld.init(g, ch0, r0a, r0b, wave, lane);
   double sq = 0.0;
-#define DMA_LOOP(MK) \
-  chunk_loop<MK, T, LAY, PREC>(g, c0, cstep, niter, buf0, buf1, nslots, r0a, r0b, wave, lane, oa, ob, d, acc, mask, sq)
-  if (mask == dma::kMaskFull) DMA_LOOP(dma::kMaskFull);
-  else if (mask == dma::kMaskUpper) DMA_LOOP(dma::kMaskUpper);
-  else if (mask == dma::kMaskHalf) DMA_LOOP(dma::kMaskHalf);
-  else if (mask == dma::kMaskCol1) DMA_LOOP(dma::kMaskCol1);
-  else if (mask == 0u) DMA_LOOP(0u);
-  else DMA_LOOP(kGeneric);
-#undef DMA_LOOP
-
+#define DMA_ITEM(MK)                                                                                              \
+  sq = item_body<MK, T, LAY, PREC, W>(g, ld, niter, buf0, buf1, diag, r0a, wave, lane, oa, o0, d, mask,           \
+                                      g.part + item * (int64_t)64 * 256)
+  // (waves without blocks still load and meet the barriers)
+  if (mask == dma::kMaskFull) DMA_ITEM(dma::kMaskFull);
+  else if (mask == dma::kMaskDiag5) DMA_ITEM(dma::kMaskDiag5);
+  else if (mask == dma::kMaskDiag4) DMA_ITEM(dma::kMaskDiag4);
+  else DMA_ITEM(kGeneric);
+#undef DMA_ITEM
   if constexpr (PREC >= 1) {
     // the item's sum of squares (zero unless diagonal), in wave order
     __shared__ double sred[kDW];
     const double sw = wave_sum(sq);
     if (lane == 0) sred[wave] = sw;
     __syncthreads();
-    if (tid == 0) g.sq[item] = (sred[0] + sred[1]) + (sred[2] + sred[3]);
-  }
-
-  // partial blocks.  MFMA result, lane l, register v: FP64 D[(l >> 4) + 4 v][l & 15],
-  // FP32 D[4 (l >> 4) + v][l & 15]
-  double* __restrict__ P = g.part + item * (int64_t)64 * 256;
-#pragma unroll
-  for (int x = 0; x < 4; ++x) {
-#pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      if ((mask >> (4 * x + y)) & 1u) {
-        const int bi = a0 + x, bj = b0 + bs * y;
-        const int qb = diag ? dma::tri_index(bi, bj) : bi * 8 + bj;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) P[(int64_t)qb * 256 + (PREC == 0 ? q + 4 * v : 4 * q + v) * 16 + i] = acc[x][y][v];
-      }
-    }
+    if (tid == 0)
+      g.sq[item] = ((sred[0] + sred[1]) + (sred[2] + sred[3])) + ((sred[4] + sred[5]) + (sred[6] + sred[7]));
   }
 }
 
@@ -510,13 +483,17 @@ __global__ __launch_bounds__(256) void gram_trace_kernel(const double* __restric
 
 }  // namespace
 
+// 16-byte loads: the base and the stride between consecutive columns (unit
+// stride) or rows (row segments) are multiples of 16 bytes; 4-byte loads
+// otherwise.
+static bool gram_dma_w16(int J, uint64_t L, int elem_size, const void* Y) {
+  return ((L == 1 ? (uint64_t)J : L) * (uint64_t)elem_size) % 16 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
+}
+
 bool gram_dma_eligible(int J, uint64_t L, int elem_size, const void* Y) {
   const uint64_t KC = 128 / elem_size;
-  // 16-byte loads: the base and the stride between consecutive columns (unit
-  // stride) or rows (row segments) must be multiples of 16 bytes
-  const uint64_t stride_bytes = (L == 1 ? (uint64_t)J : L) * (uint64_t)elem_size;
-  return J > 128 && J <= (1 << 20) && (L == 1 || L >= 64 || L % KC == 0) && stride_bytes % 16 == 0 &&
-         reinterpret_cast<uintptr_t>(Y) % 16 == 0;
+  return J > 128 && J <= (1 << 20) && (L == 1 || L >= 64 || L % KC == 0) &&
+         reinterpret_cast<uintptr_t>(Y) % elem_size == 0;
 }
 
 GramPlan plan_gram_dma(int J, uint64_t L, uint64_t K, int elem_size, int prec) {
@@ -559,17 +536,24 @@ hipError_t launch_gram_dma(const T* Y, int J, uint64_t L, uint64_t K, int prec, 
   g.part = part;
   g.sq = sq;
   const int64_t grid = ceil_div(g.total, kXcds) * kXcds;
+  const bool w16 = gram_dma_w16(J, L, (int)sizeof(T), Y);
+#define DMA_W(LAY, PREC)                                                                                          \
+  do {                                                                                                            \
+    if (w16) hipLaunchKernelGGL((gram_dma_kernel<T, LAY, PREC, 16>), dim3(grid), dim3(kDNT), 0, stream, g);       \
+    else hipLaunchKernelGGL((gram_dma_kernel<T, LAY, PREC, 4>), dim3(grid), dim3(kDNT), 0, stream, g);            \
+  } while (0)
+#define DMA_L(PREC)             \
+  do {                          \
+    if (L == 1) DMA_W(0, PREC); \
+    else DMA_W(1, PREC);        \
+  } while (0)
   if constexpr (sizeof(T) == 4) {
-    // the reduced forms take unit-stride modes only (on row segments the
-    // register-staged tile pairs measured faster)
-    if (prec != 0 && L != 1) return hipErrorInvalidValue;
-    if (prec == 1) hipLaunchKernelGGL((gram_dma_kernel<T, 0, 1>), dim3(grid), dim3(kDNT), 0, stream, g);
-    else if (prec == 3) hipLaunchKernelGGL((gram_dma_kernel<T, 0, 3>), dim3(grid), dim3(kDNT), 0, stream, g);
+    if (prec == 1) DMA_L(1);
+    else if (prec == 3) DMA_L(3);
   }
-  if (prec == 0) {
-    if (L == 1) hipLaunchKernelGGL((gram_dma_kernel<T, 0, 0>), dim3(grid), dim3(kDNT), 0, stream, g);
-    else hipLaunchKernelGGL((gram_dma_kernel<T, 1, 0>), dim3(grid), dim3(kDNT), 0, stream, g);
-  }
+  if (prec == 0) DMA_L(0);
+#undef DMA_L
+#undef DMA_W
   if (after_main) (void)hipEventRecord(after_main, stream);
   launch_gram_pair_reduce(part, p.ntiles, p.npairs, p.nsplit, J, S, stream);
   if (norm2) {

@@ -11,7 +11,8 @@
 //   layout 0 (L = 1, columns contiguous): column-major, 128 * sizeof(T) bytes
 //     per column; unit u (rows E u .. E u + E - 1) of column k is stored at
 //     unit position u ^ sw(k), with sw(k) = (k & 1) << 3 for doubles and
-//     (k & 3) << 2 for floats;
+//     (k & 3) << 2 for floats (the swizzle moves whole 16-row blocks: block b
+//     of a column is block 0's offset with b's bits flipped in);
 //   layout 1 (L > 1, row segments contiguous): row-major, 128 bytes per row;
 //     unit u (columns E u .. E u + E - 1) of row r is stored at u ^ ((r >> 1) & 7).
 // The XOR swizzles make the MFMA operand reads of a wave conflict-free:
@@ -77,41 +78,20 @@ struct Img {
 // of an 8 x 8 block tile enumerated row by row.
 __host__ __device__ inline int tri_index(int bi, int bj) { return bi * 8 - bi * (bi - 1) / 2 + (bj - bi); }
 
-// Block masks of a wave's 4 x 4 block grid (bit 4 x + y for block (x, y)).
-constexpr unsigned kMaskFull = 0xFFFFu;
-constexpr unsigned kMaskUpper = 0x8CEFu;  // x <= y
-constexpr unsigned kMaskHalf = 0x3333u;   // y < 2
-constexpr unsigned kMaskCol1 = 0x1111u;   // y = 0
-
-// The part of a tile pair's 8 x 8 blocks of 16 x 16 that wave w (of 4)
-// computes: blocks (a0 + x, b0 + bs y) of the pair's A and B tiles for the
-// bits 4 x + y set in mask.  Off-diagonal pairs: wave w takes the A blocks
-// 4 (w >> 1) .. + 3 and every other B block from w & 1 (bs = 2), so that a
-// ragged last B tile (J = 672: two blocks) gives each wave the same share
-// instead of leaving two waves idle.  Diagonal pairs need the upper triangle
-// (36 blocks, bs = 1): waves 0 and 2 take the upper 10 blocks of the diagonal
-// 4 x 4 grids, waves 1 and 3 the two 4 x 2 halves of the off-diagonal one.
-// Blocks whose rows lie at or beyond J are dropped.
-__host__ __device__ inline void wave_task(int w, bool diag, int ra, int rb, int J, int& a0, int& b0, int& bs,
-                                          unsigned& mask) {
-  if (!diag) {
-    a0 = 4 * (w >> 1);
-    b0 = w & 1;
-    bs = 2;
-    mask = kMaskFull;
-  } else if (w == 0 || w == 2) {
-    a0 = b0 = 2 * w;
-    bs = 1;
-    mask = kMaskUpper;
-  } else {
-    a0 = 0;
-    b0 = (w == 1) ? 4 : 6;
-    bs = 1;
-    mask = kMaskHalf;
-  }
-  for (int x = 0; x < 4; ++x)
-    for (int y = 0; y < 4; ++y)
-      if (ra + 16 * (a0 + x) >= J || rb + 16 * (b0 + bs * y) >= J) mask &= ~(1u << (4 * x + y));
+// The B blocks that wave w (of 8) multiplies with A block w of its tile pair:
+// slot y is B block (w + y) & 7 of a diagonal pair (so that the eight waves
+// cover every unordered pair of blocks once: offsets 0..3, and 4 for half of
+// the waves) and block y of an off-diagonal pair.  Blocks whose rows lie at or
+// beyond J are dropped.
+constexpr unsigned kMaskFull = 0xFFu;   // off-diagonal
+constexpr unsigned kMaskDiag5 = 0x1Fu;  // diagonal, w < 4
+constexpr unsigned kMaskDiag4 = 0x0Fu;  // diagonal, w >= 4
+__host__ __device__ inline int b_block(int w, bool diag, int y) { return diag ? ((w + y) & 7) : y; }
+__host__ __device__ inline unsigned wave_mask(int w, bool diag, int ra, int rb, int J) {
+  unsigned mask = !diag ? kMaskFull : (w < 4 ? kMaskDiag5 : kMaskDiag4);
+  for (int y = 0; y < 8; ++y)
+    if (ra + 16 * w >= J || rb + 16 * b_block(w, diag, y) >= J) mask &= ~(1u << y);
+  return mask;
 }
 
 }  // namespace dma

@@ -82,3 +82,26 @@ def test_slice_stats_special_values(tk, dims, n):
     v[1].flat[7] = np.nan
     st = tk.slice_stats(to_dev(X.reshape(-1), dims, torch.float64), n, dims=dims).cpu().numpy()
     assert np.isnan(st[0][1]) and np.isnan(st[1][1]) and np.isfinite(st[3][1])
+
+
+# tile pairs with direct loads: one to four row tiles, the last whole, ragged or
+# of one row; unit stride and row segments, 16-byte and 4-byte loads, chunks cut
+# by the end of a slab or of the tensor, fewer columns than a chunk
+@pytest.mark.parametrize("J", [129, 161, 249, 256, 257, 313, 400])
+@pytest.mark.parametrize("L,rest", [(1, 7), (1, 333), (64, 3), (65, 4), (66, 1), (90, 5), (128, 2)])
+def test_tile_pair_gram_edges(tk, orc, J, L, rest):
+    rng = np.random.default_rng(J * 100 + L)
+    dims, n = ([J, rest], 0) if L == 1 else ([L, J, rest], 1)
+    X = rng.standard_normal(int(np.prod(dims))).astype(np.float32).astype(np.float64)
+    ref = orc.gram(X, dims, n)
+    d = np.sqrt(np.outer(np.diag(ref), np.diag(ref)))
+    for dt, prec, tol in ((torch.float64, "fp64", 1e-11), (torch.float32, "fp64", 1e-11),
+                          (torch.float32, "fp32", 2.4e-6), (torch.float32, "bf16x6", 1.2e-5)):
+        if prec == "fp64" and J <= 240:
+            continue  # the whole triangle per workgroup
+        for offset in (0, 1):
+            buf = torch.empty(X.size + offset, dtype=dt, device="cuda")
+            buf[offset:] = torch.from_numpy(X)
+            S, nrm = tk.gram(buf[offset:], n, prec=prec, dims=dims, with_norm=True)
+            assert np.all(np.abs(S.cpu().numpy() - ref) <= tol * d), (dims, prec, offset)
+            assert abs(float(nrm[0]) - np.dot(X, X)) <= 1e-12 * np.dot(X, X)
