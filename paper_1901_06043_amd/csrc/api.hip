@@ -263,7 +263,8 @@ struct TmpBuf {
   }
 };
 
-// Small pinned host staging area for rank read-back (one per thread).
+// Small pinned host staging area, one per thread: kernels write ranks, norms
+// and flags there, and the host reads them after an event or the stream.
 struct Pinned {
   void* p = nullptr;
   ~Pinned() {
@@ -273,7 +274,7 @@ struct Pinned {
 thread_local Pinned g_pinned;
 
 tucker_status pinned(void** out) {
-  if (!g_pinned.p) HIP_TRY(hipHostMalloc(&g_pinned.p, 4096, hipHostMallocDefault));
+  if (!g_pinned.p) HIP_TRY(hipHostMalloc(&g_pinned.p, 4096, hipHostMallocCoherent));
   *out = g_pinned.p;
   return TUCKER_OK;
 }
@@ -737,9 +738,13 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
 
   void* hp = nullptr;
   if ((st = pinned(&hp))) return st;
-  int64_t* h_R = static_cast<int64_t*>(hp);
-  double* h_flag = reinterpret_cast<double*>(static_cast<char*>(hp) + 8);
-  double* h_nx2 = reinterpret_cast<double*>(static_cast<char*>(hp) + 16);
+  struct HostScalars {
+    int64_t R[TUCKER_MAX_MODES];
+    double disc[TUCKER_MAX_MODES];
+    double nx2, flag;
+  };
+  static_assert(sizeof(HostScalars) <= 4096, "fits the pinned staging area");
+  HostScalars* h = static_cast<HostScalars*>(hp);
 
   Events evs;
   HIP_TRY(evs.create(7 * N));  // 5 per step, then 2 per deferred product
@@ -820,31 +825,36 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
         HIP_TRY(tk::launch_gram_guard(Sbuf.as<double>(), (int)J, pass == 1 ? 0.0 : (double)(L * Rt),
                                       sqp ? sqp : d_sq + step, d_flag + step, stream));
       HIP_TRY(hipEventRecord(ev[1], stream));
-      HIP_TRY(tk::launch_eig_values(Sbuf.as<double>(), (int)J, thr_mul, fixed_ranks ? nullptr : d_nx2, fixed, w,
-                                    t->lam[n], t->dranks + n, d_disc + n, stream));
-      if (!async) {
-        // the rank (and flag, norm) go to the host while the eigenvectors are
-        // formed, so that the next launches are enqueued before the GPU runs
-        // out of work
-        HIP_TRY(hipMemcpyAsync(h_R, t->dranks + n, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
-        if (pp != TUCKER_GRAM_FP64)
-          HIP_TRY(hipMemcpyAsync(h_flag, d_flag + step, sizeof(double), hipMemcpyDeviceToHost, stream));
-        if (step == 0) HIP_TRY(hipMemcpyAsync(h_nx2, d_nx2, sizeof(double), hipMemcpyDeviceToHost, stream));
-        HIP_TRY(hipEventRecord(rank_ready, stream));
+      // the truncation writes the rank (and flag, norm) to the host's memory
+      // too, to be read while the eigenvectors are formed, so that the next
+      // launches are enqueued before the GPU runs out of work
+      tk::EigHost eh;
+      eh.R = &h->R[n];
+      eh.disc = &h->disc[n];
+      if (step == 0) {
+        eh.dnorm2 = d_nx2;
+        eh.norm2 = &h->nx2;
       }
+      if (pp != TUCKER_GRAM_FP64) {
+        eh.dflag = d_flag + step;
+        eh.flag = &h->flag;
+      }
+      HIP_TRY(tk::launch_eig_values(Sbuf.as<double>(), (int)J, thr_mul, fixed_ranks ? nullptr : d_nx2, fixed, w,
+                                    t->lam[n], t->dranks + n, d_disc + n, stream, eh));
+      if (!async) HIP_TRY(hipEventRecord(rank_ready, stream));
       HIP_TRY(tk::launch_eig_vectors((int)J, w, t->lam[n], t->dranks + n, t->U[n], stream));
       HIP_TRY(hipEventRecord(ev[2], stream));
       if (async) break;
       HIP_TRY(hipEventSynchronize(rank_ready));
-      if (pp == TUCKER_GRAM_FP64 || h_flag[0] == 0.0) break;
+      if (pp == TUCKER_GRAM_FP64 || h->flag == 0.0) break;
       if (pass == 0) t->scaled[n] = 1;
       else t->prec_used[n] = TUCKER_GRAM_FP64;
     }
-    const int64_t R = async ? fixed : h_R[0];
+    const int64_t R = async ? fixed : h->R[n];
     if (R < 1 || R > J) return fail(TUCKER_ENOCONV, "eigensolver returned rank %lld for J=%lld", (long long)R, (long long)J);
     if (step == 0 && !async) {
       // non-finite data shows up as a non-finite norm
-      const double nx2 = h_nx2[0];  // read back with the rank
+      const double nx2 = h->nx2;
       if (!std::isfinite(nx2)) return fail(TUCKER_EINVAL, "data contains non-finite values (||X||^2 = %g)", nx2);
       t->norm2 = nx2;
     }
@@ -966,11 +976,10 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
   t->core = ybuf.p;
   t->owned.push_back(ybuf.p);
   ybuf.p = nullptr;
-  HIP_TRY(hipMemcpyAsync(t->disc, d_disc, sizeof(double) * N, hipMemcpyDeviceToHost, stream));
-  if (async) HIP_TRY(hipMemcpyAsync(h_nx2, d_nx2, sizeof(double), hipMemcpyDeviceToHost, stream));
   HIP_TRY(hipStreamSynchronize(stream));
+  std::memcpy(t->disc, h->disc, sizeof(double) * N);
   if (async) {
-    const double nx2 = h_nx2[0];
+    const double nx2 = h->nx2;
     if (!std::isfinite(nx2)) return fail(TUCKER_EINVAL, "data contains non-finite values (||X||^2 = %g)", nx2);
     t->norm2 = nx2;
   }

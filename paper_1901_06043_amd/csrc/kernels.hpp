@@ -147,8 +147,19 @@ hipError_t launch_eig_truncate(const double* S, int J, double thr, const double*
 // are being formed: the eigenvalues and the truncation (lam, R, disc; steps
 // 1-3), then the leading R eigenvectors (U; steps 4-6), which only read w,
 // lam and R.
+// Results that the truncation also writes to pinned host memory: the rank and
+// energy (R null: nothing), and *dnorm2 and *dflag where norm2 and flag are set.
+struct EigHost {
+  int64_t* R = nullptr;
+  double* disc = nullptr;
+  const double* dnorm2 = nullptr;
+  double* norm2 = nullptr;
+  const double* dflag = nullptr;
+  double* flag = nullptr;
+};
 hipError_t launch_eig_values(const double* S, int J, double thr, const double* nx2, int fixed, const EigWork& w,
-                             double* lam, int64_t* R, double* disc, hipStream_t stream);
+                             double* lam, int64_t* R, double* disc, hipStream_t stream,
+                             const EigHost& host = EigHost{});
 hipError_t launch_eig_vectors(int J, const EigWork& w, const double* lam, const int64_t* R, double* U,
                               hipStream_t stream);
 
