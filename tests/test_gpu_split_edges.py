@@ -105,3 +105,52 @@ def test_tile_pair_gram_edges(tk, orc, J, L, rest):
             S, nrm = tk.gram(buf[offset:], n, prec=prec, dims=dims, with_norm=True)
             assert np.all(np.abs(S.cpu().numpy() - ref) <= tol * d), (dims, prec, offset)
             assert abs(float(nrm[0]) - np.dot(X, X)) <= 1e-12 * np.dot(X, X)
+
+
+def _tri_case(kind, J):
+    """Symmetric matrices that are hard for counting eigenvalues by minors."""
+    rng = np.random.default_rng(J)
+    S = np.zeros((J, J))
+    if kind == "integer":  # diagonal, exactly hit, many equal
+        S = np.diag(rng.integers(0, 4, J).astype(float))
+    elif kind == "blocks":  # decoupled, the same pair of eigenvalues in each
+        for i in range(0, J - 1, 2):
+            S[i:i + 2, i:i + 2] = [[2.0, 1.0], [1.0, 2.0]]
+    elif kind == "toeplitz":  # tridiagonal already, minors that vanish exactly
+        S = 2.0 * np.eye(J) + np.eye(J, k=1) + np.eye(J, k=-1)
+    elif kind in ("graded", "tiny", "huge"):
+        Q = np.linalg.qr(rng.standard_normal((J, J)))[0]
+        S = (Q * 10.0 ** np.linspace(0, -18, J)) @ Q.T
+        S = 0.5 * (S + S.T) * {"graded": 1.0, "tiny": 1e-90, "huge": 1e90}[kind]
+    return S
+
+
+# rows in groups of 8 and their neighbours, one and several rounds of 64 tails
+@pytest.mark.parametrize("J", [1, 2, 7, 8, 9, 63, 64, 65, 128, 129, 200])
+@pytest.mark.parametrize("kind", ["zero", "integer", "blocks", "toeplitz", "graded", "tiny", "huge"])
+def test_eigenvalue_counts_and_truncation(tk, orc, J, kind):
+    S = _tri_case(kind, J)
+    ref = np.linalg.eigvalsh(S)[::-1]
+    nS = np.abs(ref).max()
+    tail = np.concatenate([np.cumsum(np.clip(ref, 0, None)[::-1])[::-1], [0.0]])
+    for R0 in sorted({1, 2, J // 2 + 1, J}):
+        if R0 > J:
+            continue
+        thr = 0.5 * (tail[R0] + tail[R0 - 1])
+        lam, U, R, disc = tk.eig_truncate(torch.from_numpy(S).cuda(), thr)
+        lam = lam.cpu().numpy()
+        assert np.abs(lam - ref).max() <= 1e-12 * nS
+        assert R >= 1 and tail[R] <= thr + 1e-12 * J * nS and (R == 1 or tail[R - 1] >= thr - 1e-12 * J * nS)
+        assert abs(disc - tail[R]) <= 1e-12 * J * nS
+
+
+@pytest.mark.parametrize("J", [1, 8, 63, 65, 128])
+def test_eigenvalue_counts_in_a_batch(tk, J):
+    """Diagonal unfoldings: eigenvalues that the counts hit exactly, and none but zero."""
+    d = (np.arange(J) % 4).astype(np.float32)
+    xs = [to_dev(np.diag(d).reshape(-1), [J, J], torch.float32), to_dev(np.zeros(J * J), [J, J], torch.float32),
+          to_dev(np.eye(J).reshape(-1), [J, J], torch.float32)]
+    b = tk.Batch(xs, 1e-4, prec="fp64", dims=[[J, J]] * 3)
+    b.run()
+    nz = max(1, int(np.count_nonzero(d)))
+    assert b.ranks() == [[nz, nz], [1, 1], [J, J]]
