@@ -8,7 +8,7 @@
 // This GPU version does exactly that, with published methods:
 //  1. Householder reduction to tridiagonal form T = Q^T S Q.  Per step:
 //     p = tau A v, w = p - (tau/2)(p.v) v, A <- A - v w^T - w v^T.
-//     Once the trailing matrix has at most 208 rows, one workgroup keeps it in
+//     Once the trailing matrix has at most 192 rows, one workgroup keeps it in
 //     registers (each matrix row on 16 lanes of a wave), in phases of shrinking
 //     register layouts; the matrix-vector products and the rank-2 updates run
 //     from registers, with look-ahead (the owner of the next row publishes it
@@ -78,17 +78,19 @@ __device__ __forceinline__ double block_max(double v, double* sred) {
   return s;
 }
 
-// ---------------------------------------------------------------- 1a. tridiagonalisation, J <= 208
+// ---------------------------------------------------------------- 1a. tridiagonalisation, J <= 192
 // The full symmetric matrix is held in registers.  Each row of 16 lanes of a
 // wave holds one matrix row: lane l serves row slot l >> 4 and the columns
 // (l & 15) + 16 c, c < NC; wave w, group g, slot s holds row 4 (NW g + w) + s.
 // Every reduction (row sums, norms, dot products) is then a 16-lane DPP
 // reduction, bit-identical in all lanes, and the barriers order LDS only.
-// Row groups that are already reduced are skipped; reduced columns carry
-// v_j = w_j = 0 and are processed without branches.
+// Reduced rows and columns carry v = w = 0 and are processed without branches.
 // Output: d, e, tau and, in row k of H, the Householder vector v_k at
 // positions k+2..J-1 (implicit 1 at k+1).
-constexpr int kRegMaxJ = 208;
+// (A phase of 13 x 13 for up to 208 rows in 4 waves took 83 us for the 8 steps of
+// a 200-row matrix, in accumulation registers; the steps over rows in memory,
+// below, take 62 us.)
+constexpr int kRegMaxJ = 192;
 
 // Householder scalars of a step from alpha = a_k,k+1 and sigma =
 // sum_{j >= k+2} a_kj^2: beta = -sign(alpha) sqrt(alpha^2 + sigma),
@@ -97,7 +99,10 @@ constexpr int kRegMaxJ = 208;
 // would lose precision in the subnormal range (rows of a strongly graded
 // matrix), so the caller passes the values of the row scaled by kRowScale and
 // reflector() unscales beta and scale (tau is scale-free), as LAPACK's
-// reflector generator does.
+// reflector generator does.  Every step waits for these scalars: the square root,
+// its reciprocal and 1 / (alpha - beta) come from the hardware estimates, refined
+// to the last place, with one correction each for beta and tau (55 against 57 us
+// for 64 rows with the library's square root and two divisions).
 constexpr double kTinyNorm2 = 0x1p-900;
 constexpr double kRowScale = 0x1p+600;
 __device__ __forceinline__ bool row_is_tiny(double alpha, double sigma) {
@@ -109,9 +114,24 @@ __device__ __forceinline__ void reflector(double alpha, double sigma, bool scale
   tk = 0.0;
   scale = 0.0;
   if (sigma != 0.0) {
-    beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
-    tk = (beta - alpha) / beta;
-    scale = 1.0 / (alpha - beta);
+    const double n2 = fma(alpha, alpha, sigma);
+    const double y = __builtin_amdgcn_rsq(n2);
+    double g = n2 * y, h = 0.5 * y;
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      const double r = fma(-g, h, 0.5);
+      g = fma(g, r, g);
+      h = fma(h, r, h);
+    }
+    g = fma(fma(-g, g, n2), h, g);
+    const double x = fabs(alpha) + g;
+    double rx = __builtin_amdgcn_rcp(x);
+    rx = fma(rx, fma(-x, rx, 1.0), rx);
+    rx = fma(rx, fma(-x, rx, 1.0), rx);
+    const double q = x * (h + h);
+    beta = -copysign(g, alpha);
+    tk = fma(fma(-q, g, x), h + h, q);
+    scale = copysign(rx, alpha);
   }
   if (scaled) {
     beta *= 1.0 / kRowScale;
@@ -119,55 +139,54 @@ __device__ __forceinline__ void reflector(double alpha, double sigma, bool scale
   }
 }
 
-// Sum of (kRowScale x_j)^2 over this lane's columns j >= kk + 2 of the row x in LDS.
+// Row kk of the matrix, r in the 16 lanes of its slot (`mine`) of the owner wave,
+// becomes the vector of step kk: its reflector scalars from the values in
+// registers (sigma = sum_{j >= kk+2} r_j^2, alpha = r_kk+1), then
+// v = (0 .. 0, 1, r_j scale) to sv, beta and tau to ssn[0..1] and, when this
+// phase takes that step (`store`), d, e and tau of row kk to memory.
 template <int NC>
-__device__ __forceinline__ double scaled_tail(const double* x, int c, int kk, int J) {
+__device__ __forceinline__ void publish_row(int kk, int J, bool mine, int c, const double (&r)[NC], double* sx,
+                                            double* sv, double* ssn, bool store, double* d, double* e,
+                                            double* tau) {
   double part = 0.0;
 #pragma unroll
   for (int cc = 0; cc < NC; ++cc) {
     const int j = c + 16 * cc;
-    const double y = x[j] * kRowScale;
-    part += (j >= kk + 2 && j < J) ? y * y : 0.0;
+    if (mine) sx[j] = r[cc];
+    part += (j >= kk + 2 && j < J) ? r[cc] * r[cc] : 0.0;
   }
-  return part;
-}
-
-// Row kk of the matrix becomes the column of step kk: its owner wave writes
-// it to LDS and computes that step's reflector scalars from the values in its
-// registers (sigma = sum_{j >= kk+2} a_kk,j^2, alpha = a_kk,kk+1,
-// beta = -sign(alpha) sqrt(alpha^2 + sigma), tau = (beta - alpha) / beta,
-// scale = 1 / (alpha - beta)), published in ssn[0..2].  Called by every wave;
-// only the owner acts.
-template <int NW, int NG, int NC>
-__device__ __forceinline__ void publish_row(int kk, int J, int wave, int rs, int c, const double (&a)[NG][NC],
-                                            double* sxn, double* ssn) {
-  const int blk = kk >> 2;
-  if (wave != blk % NW) return;  // uniform
-  const int gk = blk / NW;
-  const bool mine = (rs == (kk & 3));
-  double part = 0.0;
-#pragma unroll
-  for (int g = 0; g < NG; ++g)
-    if (g == gk) {
-#pragma unroll
-      for (int cc = 0; cc < NC; ++cc) {
-        const int j = c + 16 * cc;
-        const double x = a[g][cc];
-        if (mine) sxn[j] = x;
-        part += (j >= kk + 2 && j < J) ? x * x : 0.0;
-      }
-    }
-  double sigma = row16_sum(part);  // the owner slot's 16 lanes hold row kk
-  if (kk + 1 >= J) return;
-  double alpha = sxn[kk + 1];  // written above by this wave (LDS operations of a wave are ordered)
+  double sigma = row16_sum(part);
+  // written above by this wave (LDS operations of a wave are ordered); kk + 1 < J
+  double alpha = sx[kk + 1];
+  const double diag = sx[kk];
   const bool tiny = row_is_tiny(alpha, sigma);  // uniform within each 16-lane row
-  if (tiny) sigma = row16_sum(scaled_tail<NC>(sxn, c, kk, J)), alpha *= kRowScale;
+  if (tiny) {
+    part = 0.0;
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) {
+      const int j = c + 16 * cc;
+      const double y = r[cc] * kRowScale;
+      part += (j >= kk + 2 && j < J) ? y * y : 0.0;
+    }
+    sigma = row16_sum(part);
+    alpha *= kRowScale;
+  }
   double beta, tk, scale;
   reflector(alpha, sigma, tiny, beta, tk, scale);
-  if (mine && c == 0) {
-    ssn[0] = beta;
-    ssn[1] = tk;
-    ssn[2] = scale;
+  if (mine) {
+#pragma unroll
+    for (int cc = 0; cc < NC; ++cc) {
+      const int j = c + 16 * cc;
+      sv[j] = (j <= kk || j >= J) ? 0.0 : (j == kk + 1 ? 1.0 : r[cc] * scale);
+    }
+    if (c == 0) {
+      ssn[0] = tk;
+      if (store) {
+        d[kk] = diag;
+        e[kk] = beta;
+        tau[kk] = tk;
+      }
+    }
   }
 }
 
@@ -178,19 +197,31 @@ __device__ __forceinline__ void publish_row(int kk, int J, int wave, int rs, int
 // read it in place.  d, e, tau and H (leading dimension ldh) start at the
 // block's first row.  Waves numbered NW and above hold no rows: they only
 // take part in the barriers.
-// Look-ahead: during the update of step k the wave owning row k + 1 (in its
-// first live group) writes that row to LDS as soon as it is updated and
-// computes the scalars of step k + 1 from its registers, so a step starts
-// from LDS values instead of a reduction, square root and divisions on every
-// wave.  Columns and scalars are double-buffered by the parity of k: one
-// barrier after the matrix-vector product and one at the end of each step.
+// Look-ahead: in the update of step k the wave owning row k + 1 first forms
+// that row, computes the scalars of step k + 1 from it and writes its vector
+// to LDS, while the other waves update, so a step starts from LDS values
+// instead of a reduction, square root and divisions on every wave.  Vectors
+// and scalars are double-buffered by the parity of k: one barrier after the
+// matrix-vector product and one at the end of each step.
+// A step is a chain of short operations (0.8 us for 32 rows, 1.7 us for 128), so
+// the row groups of a wave run side by side: no branch leaves out those that are
+// reduced already (their v_i and w_i are zero).  Whole reductions of 64 and 128
+// rows, with that branch and a published row that every wave scaled for itself:
+// 64 and 174 us; now 55 and 150 us.  Also tried: one barrier per step, with every
+// wave forming the next vector for itself (66 us for 64 rows in 8 waves, 86 in
+// 16); v and w read again from LDS instead of held (59); 8 waves (56).
 template <int NW, int NG, int NC>
 __device__ __forceinline__ void tridiag_reg_body(const double* S, int lds, int J, int nsteps, double* Aout, int lda,
                                                  double* __restrict__ H, int ldh, double* __restrict__ d,
                                                  double* __restrict__ e, double* __restrict__ tau) {
-  __shared__ double sxb[2][16 * NC];  // column k of the current matrix (by parity of k)
-  __shared__ double ssc[2][4];        // beta, tau, scale of step k (by parity of k)
-  __shared__ double sp[16 * NC];      // p = tau A v
+  constexpr int kCols = 16 * NC, kRows = 4 * NW * NG, kLen = kRows > kCols ? kRows : kCols;
+  // the next row before the update where registers hold it beside the matrix
+  // (4 x 6 x 6 for 96 matrices: 57 us, after it 59)
+  constexpr bool kFirst = NG * NC <= 36;
+  __shared__ double sx[kCols];     // the row being published
+  __shared__ double svb[2][kLen];  // v of step k (by parity of k); zero outside k+1 .. J-1
+  __shared__ double ssc[2];        // tau of step k (by parity of k)
+  __shared__ double sp[kLen];      // p = tau A v; zero outside k+1 .. J-1
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, rs = lane >> 4;
@@ -211,99 +242,82 @@ __device__ __forceinline__ void tridiag_reg_body(const double* S, int lds, int J
       const int i = 4 * (NW * g + wave) + rs, j = c + 16 * cc;
       a[g][cc] = (i < J && j < J) ? S[(int64_t)i * lds + j] : 0.0;
     }
-  for (int j = tid; j < 16 * NC; j += 64 * NW) sp[j] = 0.0;
-  publish_row<NW, NG, NC>(0, J, wave, rs, c, a, sxb[0], ssc[0]);
+  for (int j = tid; j < kLen; j += 64 * NW) {
+    sp[j] = 0.0;
+    if (j >= kCols) svb[0][j] = svb[1][j] = 0.0;  // the columns are written with each vector
+  }
+  if (wave == 0 && J >= 2) publish_row<NC>(0, J, rs == 0, c, a[0], sx, svb[0], &ssc[0], nsteps > 0, d, e, tau);
   lds_barrier();
 
   int k = 0;
   for (; k + 2 < J && k < nsteps; ++k) {
-    const double* sx = sxb[k & 1];
-    double* sxn = sxb[(k + 1) & 1];
-    double* ssn = ssc[(k + 1) & 1];
-    const double beta = ssc[k & 1][0], tk = ssc[k & 1][1], scale = ssc[k & 1][2];
-    if (tid == 0) {
-      d[k] = sx[k];
-      e[k] = beta;
-      tau[k] = tk;
-    }
-    if (wave == 0)
-      for (int j = k + 2 + lane; j < J; j += 64) H[(int64_t)k * ldh + j] = sx[j] * scale;
-    // (tau = 0 needs no special case: p, w and the update vanish).  LDS reads
-    // are unconditional (then selected) so that they are issued together.
-    double vj[NC];
+    const double* sv = svb[k & 1];
+    const double tk = ssc[k & 1];
+    double vj[NC], vi[NG], t[NG];
 #pragma unroll
-    for (int cc = 0; cc < NC; ++cc) {
-      const int j = c + 16 * cc;
-      const double x = sx[j];
-      vj[cc] = (j <= k || j >= J) ? 0.0 : (j == k + 1 ? 1.0 : x * scale);
-    }
-    // p_i = tau * sum_j a_ij v_j
+    for (int cc = 0; cc < NC; ++cc) vj[cc] = sv[c + 16 * cc];
+    // p_i = tau * sum_j a_ij v_j (tau = 0 needs no special case: p, w and the
+    // update vanish; columns <= k have v_j = 0 and contribute nothing)
+#pragma unroll
+    for (int g = 0; g < NG; ++g) t[g] = a[g][0] * vj[0];
+#pragma unroll
+    for (int cc = 1; cc < NC; ++cc)
+#pragma unroll
+      for (int g = 0; g < NG; ++g) t[g] = fma(a[g][cc], vj[cc], t[g]);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) t[g] = row16_sum(t[g]);
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       const int i = 4 * (NW * g + wave) + rs;
-      if (4 * (NW * g + wave) + 3 <= k) {  // whole group reduced (uniform): p = 0 there
-        if (c == 0 && i < J) sp[i] = 0.0;
-        continue;
-      }
-      // columns <= k have v_j = 0 and contribute nothing
-      double t = 0.0;
-#pragma unroll
-      for (int cc = 0; cc < NC; ++cc) t += a[g][cc] * vj[cc];
-      t = row16_sum(t);
-      if (c == 0 && i < J) sp[i] = (i > k) ? tk * t : 0.0;
+      if (c == 0) sp[i] = (i > k && i < J) ? tk * t[g] : 0.0;
     }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) vi[g] = sv[4 * (NW * g + wave) + rs];
     lds_barrier();
+    double wj[NC], wi[NG];
     double pv = 0.0;
 #pragma unroll
-    for (int cc = 0; cc < NC; ++cc) pv += sp[c + 16 * cc] * vj[cc];
+    for (int cc = 0; cc < NC; ++cc) {
+      wj[cc] = sp[c + 16 * cc];
+      pv += wj[cc] * vj[cc];
+    }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) wi[g] = sp[4 * (NW * g + wave) + rs];
     pv = row16_sum(pv);
     const double c2 = 0.5 * tk * pv;
-    // A <- A - v w^T - w v^T on the live rows and column slots, w = p - c2 v.
-    // The owner of row k + 1 (whose first live group holds it) writes that row
-    // to LDS as soon as it is updated and sums the squares of its tail.
-    const int kn = k + 1, blkn = kn >> 2;
-    const int gkn = (wave == blkn % NW) ? blkn / NW : -1;  // uniform
-    const bool slot = (rs == (kn & 3));
-    double part = 0.0;
+    // A <- A - v w^T - w v^T, w = p - c2 v; zero for reduced rows and columns
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      if (4 * (NW * g + wave) + 3 <= k) continue;  // uniform
-      const int i = 4 * (NW * g + wave) + rs;
-      const int ic = min(i, 16 * NC - 1);  // rows beyond the columns are padding
-      const double sxi = sx[ic], spi = sp[ic];
-      const double vi = (i <= k || i >= J) ? 0.0 : (i == k + 1 ? 1.0 : sxi * scale);
-      const double wi = (i < J) ? spi - c2 * vi : 0.0;
+    for (int cc = 0; cc < NC; ++cc) wj[cc] -= c2 * vj[cc];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) wi[g] -= c2 * vi[g];
+    const int kn = k + 1, blkn = kn >> 2;
+    auto update = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int cc = 0; cc < NC; ++cc) a[g][cc] = fma(-vi[g], wj[cc], fma(-wi[g], vj[cc], a[g][cc]));
+    };
+    if (!kFirst) update();
+    if (wave == blkn % NW) {  // uniform
+      double r[NC];
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+        if (NG == 1 || g == blkn / NW) {
+#pragma unroll
+          for (int cc = 0; cc < NC; ++cc)
+            r[cc] = kFirst ? fma(-vi[g], wj[cc], fma(-wi[g], vj[cc], a[g][cc])) : a[g][cc];
+        }
+      publish_row<NC>(kn, J, rs == (kn & 3), c, r, sx, svb[kn & 1], &ssc[kn & 1], kn < nsteps, d, e, tau);
+    } else if (wave == (blkn + 1) % NW && rs == 0) {
 #pragma unroll
       for (int cc = 0; cc < NC; ++cc) {
-        const double wj = sp[c + 16 * cc] - c2 * vj[cc];  // w_j; zero for reduced columns
-        a[g][cc] = fma(-vi, wj, fma(-wi, vj[cc], a[g][cc]));
-      }
-      if (g == gkn) {
-#pragma unroll
-        for (int cc = 0; cc < NC; ++cc) {
-          const int j = c + 16 * cc;
-          if (slot) sxn[j] = a[g][cc];
-          part += (j >= kn + 2 && j < J) ? a[g][cc] * a[g][cc] : 0.0;
-        }
+        const int j = c + 16 * cc;
+        if (j >= k + 2 && j < J) H[(int64_t)k * ldh + j] = vj[cc];
       }
     }
-    if (gkn >= 0 && kn + 1 < J) {
-      // scalars of step k + 1 from the owner slot's 16 lanes
-      double sigma = row16_sum(part);
-      double alpha = sxn[kn + 1];  // written above by this wave (LDS operations of a wave are ordered)
-      const bool tiny = row_is_tiny(alpha, sigma);  // uniform within each 16-lane row
-      if (tiny) sigma = row16_sum(scaled_tail<NC>(sxn, c, kn, J)), alpha *= kRowScale;
-      double nbeta, ntk, nscale;
-      reflector(alpha, sigma, tiny, nbeta, ntk, nscale);
-      if (slot && c == 0) {
-        ssn[0] = nbeta;
-        ssn[1] = ntk;
-        ssn[2] = nscale;
-      }
-    }
+    if (kFirst) update();
     lds_barrier();
   }
-  const double* sx = sxb[k & 1];
   if (k + 2 < J) {
     // stopped early: hand the trailing block (rows and columns >= k) to the next phase
 #pragma unroll
@@ -318,22 +332,15 @@ __device__ __forceinline__ void tridiag_reg_body(const double* S, int lds, int J
     }
     return;
   }
-  if (J >= 2) {
-    if (tid == 0) {
-      d[J - 2] = sx[J - 2];
-      e[J - 2] = sx[J - 1];
-    }
-    const int kl = J - 1, blk = kl >> 2;
-    if (wave == blk % NW && rs == (kl & 3) && c == (kl & 15)) {
-      const int gk = blk / NW, ck = kl >> 4;
+  // the last diagonal entry (row J - 2 was published as a step's)
+  const int kl = J - 1, blk = kl >> 2;
+  if (wave == blk % NW && rs == (kl & 3) && c == (kl & 15)) {
+    const int gk = blk / NW, ck = kl >> 4;
 #pragma unroll
-      for (int g = 0; g < NG; ++g)
+    for (int g = 0; g < NG; ++g)
 #pragma unroll
-        for (int cc = 0; cc < NC; ++cc)
-          if (g == gk && cc == ck) d[kl] = a[g][cc];
-    }
-  } else if (tid == 0) {
-    d[0] = sx[0];
+      for (int cc = 0; cc < NC; ++cc)
+        if (g == gk && cc == ck) d[kl] = a[g][cc];
   }
 }
 
@@ -383,11 +390,11 @@ __global__ __launch_bounds__(1024) void eig_tridiag_tail_kernel(const double* S,
   TAIL_PHASE(16, 2, 8, 96)
   TAIL_PHASE(16, 2, 6, 64)
   TAIL_PHASE(16, 1, 4, 32)
-#undef TAIL_PHASE
   tridiag_reg_body<8, 1, 2>(src, lsrc, Jl, Jl, hand, 32, H, ld, d, e, tau);
+#undef TAIL_PHASE
 }
 
-// ---------------------------------------------------------------- 1b. tridiagonalisation steps, J > 208
+// ---------------------------------------------------------------- 1b. tridiagonalisation steps, J > 192
 // While the trailing matrix is larger than the register-resident form holds,
 // each Householder step is a launch over blocks of kBigRows matrix rows
 // (A: J x J in global memory, global indices).  A step needs two passes that
@@ -2318,8 +2325,8 @@ hipError_t launch_eig_values(const double* S, int J, double thr, const double* n
         next = 0;
         hipLaunchKernelGGL(eig_tridiag_tail_kernel, dim3(1), dim3(1024), sizeof(double) * kTailHand, stream, src, ld,
                            k0, J, w.A, w.d, w.e, w.tau);
-      } else if (Jl <= 192) { next = 128; TRI_LAUNCH(8, 6, 12); }
-      else { next = 192; TRI_LAUNCH(4, 13, 13); }  // Jl <= kRegMaxJ
+      } else if (Jl <= 160) { next = 128; TRI_LAUNCH(8, 5, 10); }
+      else { next = 160; TRI_LAUNCH(8, 6, 12); }  // Jl <= kRegMaxJ
 #undef TRI_LAUNCH
       LAUNCH_OK();
       if (next == 0) break;

@@ -154,3 +154,23 @@ def test_eigenvalue_counts_in_a_batch(tk, J):
     b.run()
     nz = max(1, int(np.count_nonzero(d)))
     assert b.ranks() == [[nz, nz], [1, 1], [J, J]]
+
+
+# one row short of, at and past the 160-row phase, and either side of the others
+@pytest.mark.parametrize("J", [4, 31, 95, 127, 159, 160, 161, 191, 194, 225])
+def test_tridiagonalisation_phase_edges(tk, J):
+    """Eigenpairs of a full matrix with 17 zero rows and columns (tau = 0) for J > 31;
+    residual within 1e-11 ||S||, orthogonality within 1e-11 (u over the gap of 1e-3 ||S||
+    from which inverse iteration is left to itself)."""
+    rng = np.random.default_rng(J)
+    A = rng.standard_normal((J, J + 3))
+    if J > 31:
+        A[J // 2:J // 2 + 17] = 0.0
+    S = A @ A.T
+    lam, U, R, _ = tk.eig_truncate(torch.from_numpy(S).cuda(), 1e-13 * np.trace(S))
+    lam, U = lam.cpu().numpy(), U.cpu().numpy()
+    ref = np.linalg.eigvalsh(S)[::-1]
+    assert np.abs(lam - ref).max() <= 1e-12 * ref[0]
+    assert R == (J if J <= 31 else J - 17)
+    assert np.abs(U.T @ U - np.eye(R)).max() <= 1e-11
+    assert np.linalg.norm(S @ U - U * lam[:R], 2) <= 1e-11 * ref[0]
