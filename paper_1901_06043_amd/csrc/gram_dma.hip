@@ -15,11 +15,12 @@
 // cover each other's operand reads, load issue and barriers.  Four waves of
 // 64 x 64 (two per SIMD) covered them less, and the reduced forms, which keep
 // FP32 sums or bf16 pieces beside the FP64 accumulators, fitted only one such
-// workgroup on a CU; with one block column at a time they now fit two.
+// workgroup on a CU; with eight waves they have two per SIMD in one workgroup,
+// or, with 4-byte loads, four in two.
 // J^2 K flops over the time, before and after: FP64 672x448x33x64 doubles,
 // mode 0: 46.7 -> 58 TF, mode 1 of 448x672x33x64: 45.6 -> 55 TF (FP64 MFMA
 // bound, with 4 TB/s of tile reads beyond L2 close behind); FP32 mode 0 of
-// 672x448x33x64: 52 -> 73 TF; 161x161x160x11x25 (unaligned columns, on the
+// 672x448x33x64: 52 -> 83 TF; 161x161x160x11x25 (unaligned columns, on the
 // register-staged kernel before): FP32 20.6 -> 49, BF16X6 15.9 -> 46 TF.
 // Blocks of rows at or beyond J are skipped, so a ragged last tile costs only
 // its rows.  About 8192 items: the faster diagonal and ragged items then even
@@ -247,8 +248,8 @@ constexpr unsigned kGeneric = 0x100u;
 // PREC 0: FP64 products and accumulation, step by step over all slots.
 // PREC 1 (FP32 MFMA) and 3 (BF16X6), float input: slot by slot, each slot's
 // products summed in FP32 over the chunk's 32 columns (BF16X6: smallest terms
-// first), then added to its FP64 accumulator.
-template <unsigned MK, typename T, int LAY, int PREC>
+// first), then added to its FP64 accumulator; AHEAD: FP32 slots overlap.
+template <unsigned MK, typename T, int LAY, int PREC, bool AHEAD>
 __device__ __forceinline__ void compute_chunk(const char* abuf, const char* bbuf, int oa, int ob, int d, int b0,
                                               d4 (&acc)[8], unsigned mask) {
   using I = Img<sizeof(T), LAY>;
@@ -289,6 +290,36 @@ __device__ __forceinline__ void compute_chunk(const char* abuf, const char* bbuf
         for (int y = 0; y < 8; ++y)
           if (on(y)) acc[y] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s], (double)b[y][s], acc[y], 0, 0, 0);
     }
+  } else if constexpr (PREC == 1 && AHEAD && MK != kGeneric) {
+    // the next slot's operands are read before, and a slot's sums added to the
+    // FP64 accumulators under, the products of another slot
+    float a[8], b[2][8];
+    f4 c[2];
+    read8<LAY>(abuf, oa, d, a);
+    read8<LAY>(bbuf, boff(__builtin_ctz(MK)), d, b[0]);
+    int n = 0, prev = -1;
+#pragma unroll
+    for (int y = 0; y < 8; ++y) {
+      if (!on(y)) continue;
+#pragma unroll
+      for (int z = y + 1; z < 8; ++z)
+        if (on(z)) {
+          read8<LAY>(bbuf, boff(z), d, b[(n + 1) & 1]);
+          break;
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      c[n & 1] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 8; ++s) c[n & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[n & 1][s], c[n & 1], 0, 0, 0);
+      if (prev >= 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[prev][v] += (double)c[(n + 1) & 1][v];
+      }
+      prev = y;
+      ++n;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[prev][v] += (double)c[(n + 1) & 1][v];
   } else {
     float a[8];
     read8<LAY>(abuf, oa, d, a);
@@ -366,7 +397,7 @@ __device__ __forceinline__ void chunk_loop(const DmaParams& g, Loader<T, LAY, W>
     if (more) ld.issue(nxt, nslots, wave, lane);  // uniform
     if constexpr (PREC >= 1)
       if (dsq) sq += chunk_sq<LAY>(cur, r0a, g.J, tid);
-    compute_chunk<MK, T, LAY, PREC>(cur, cur + pb, oa, ob, d, b0, acc, mask);
+    compute_chunk<MK, T, LAY, PREC, W == 16>(cur, cur + pb, oa, ob, d, b0, acc, mask);
     if (more) {
       __builtin_amdgcn_s_waitcnt(0);
       ld.finish(g, nxt, nslots, wave, lane);
@@ -414,12 +445,15 @@ __device__ __forceinline__ double item_body(const DmaParams& g, Loader<T, LAY, W
   return sq;
 }
 
-// BF16X6 with 16-byte loads runs one workgroup per CU: the pieces of two
-// operand blocks beside the accumulators spill at 128 registers (4.2 against
-// 3.6 ms for a 256x256x256x11x5 mode); with 4-byte loads, whose issue needs
-// covering, two workgroups are the faster (4.0 against 5.6 ms, 161x161x160x11x25).
+// The reduced forms with 16-byte loads run one workgroup per CU: the pieces of
+// two operand blocks (BF16X6), or two slots' operands and sums (FP32, AHEAD),
+// beside the accumulators spill at 128 registers (mode 0 of 256x256x256x11x5:
+// BF16X6 3.6 against 4.2 ms with two workgroups, FP32 3.0 against 3.3 ms with
+// two and no overlap of slots, 3.4 with it); with 4-byte loads, whose issue
+// needs covering, two workgroups are the faster (mode 0 of 161x161x160x11x25:
+// BF16X6 4.0 against 5.6 ms, FP32 3.7 against 4.8 ms).
 template <typename T, int LAY, int PREC, int W>
-__global__ __launch_bounds__(kDNT, PREC == 3 && W == 16 ? 2 : 4) void gram_dma_kernel(DmaParams g) {
+__global__ __launch_bounds__(kDNT, PREC != 0 && W == 16 ? 2 : 4) void gram_dma_kernel(DmaParams g) {
   static_assert(PREC == 0 || sizeof(T) == 4, "the reduced forms read float input");
   using I = Img<sizeof(T), LAY>;
   __shared__ __attribute__((aligned(16))) char buf0[2 * I::TB];
