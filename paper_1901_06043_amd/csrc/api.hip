@@ -402,10 +402,19 @@ tucker_status pack_factor(const double*& M, int64_t& msk, int64_t& msj, int64_t 
   return TUCKER_OK;
 }
 
+// Scratch that only makes a call faster: none while the stream is being captured
+// (an allocation would end the capture) or where the allocation fails.
+bool optional_scratch(TmpBuf& b, size_t bytes, hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+  if (b.alloc(bytes, s) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
 // `scratch` (may be null): K * (J + 1) doubles for an aligned copy of M, free
 // until the work enqueued here has run; null allocates the copy where one is
-// needed (not on a capturing stream, which takes the kernel that reads M as
-// it is).
+// needed (without it the kernel that reads M as it is takes the product).
 tucker_status run_ttm(const void* Y, tucker_dtype yd, const int64_t* dims, int N, int n, const double* M,
                       int64_t K, int64_t msk, int64_t msj, void* Z, tucker_dtype zd, bool f32p, hipStream_t s,
                       double* scratch = nullptr) {
@@ -417,13 +426,7 @@ tucker_status run_ttm(const void* Y, tucker_dtype yd, const int64_t* dims, int N
     return fail(TUCKER_EUNSUPPORTED, "TTM of mode %d too large for 32-bit column indexing", n);
   TmpBuf packed;
   if (!f32p && tk::ttm_dma_wants_pack((int)J, (uint64_t)cols, (int)K, msk, msj, (int)dtype_size(yd), Y, M)) {
-    if (!scratch) {
-      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
-        HIP_TRY(packed.alloc(sizeof(double) * K * (J + 1), s));
-        scratch = packed.as<double>();
-      }
-    }
+    if (!scratch && optional_scratch(packed, sizeof(double) * K * (J + 1), s)) scratch = packed.as<double>();
     tucker_status st;
     if (scratch && (st = pack_factor(M, msk, msj, K, J, scratch, s))) return st;
   }
@@ -1313,8 +1316,9 @@ tucker_status reconstruct_impl(const tucker_t* t, const tucker_op* ops, const in
       msj[k] = t->dims[k];
       if (!f32p && tk::ttm_dma_wants_pack((int)t->ranks[k], 1, (int)K[k], 1, msj[k], 8, nullptr, M[k])) {
         // odd mode size or begin
-        HIP_TRY(wbuf[k].alloc(sizeof(double) * K[k] * (t->ranks[k] + 1), stream));
-        if ((st = pack_factor(M[k], msk[k], msj[k], K[k], t->ranks[k], wbuf[k].as<double>(), stream))) return st;
+        if (optional_scratch(wbuf[k], sizeof(double) * K[k] * (t->ranks[k] + 1), stream) &&
+            (st = pack_factor(M[k], msk[k], msj[k], K[k], t->ranks[k], wbuf[k].as<double>(), stream)))
+          return st;
       }
       continue;
     }

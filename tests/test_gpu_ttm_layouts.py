@@ -133,3 +133,16 @@ def test_ttm_small_slabs_infinity(tk):
     want = torch.zeros((3, 7, 8), dtype=torch.float64)
     want[1, :, 3] = float("inf")
     assert torch.equal(z.cpu(), want)
+
+
+def test_ttm_without_scratch(tk):
+    """A factor that would be laid out again is read as it is where no memory is given."""
+    import ctypes
+    alloc, free = (f[1] for f in tk._Allocator._fields_[:2])
+    none = tk._Allocator(alloc(lambda nbytes, ctx, stream: None), free(lambda p, ctx, stream: None), None)
+    assert tk.lib().tucker_set_allocator(ctypes.byref(none)) == 0
+    try:
+        check(tk, [33, 50, 7], 1, 71, "columns", np.float64, np.float64, offset=1)
+        check(tk, [33, 51, 7], 0, 71, "rows", np.float32, np.float64)
+    finally:
+        assert tk.lib().tucker_set_allocator(None) == 0
