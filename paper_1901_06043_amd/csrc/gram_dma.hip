@@ -524,10 +524,33 @@ static bool gram_dma_w16(int J, uint64_t L, int elem_size, const void* Y) {
   return ((L == 1 ? (uint64_t)J : L) * (uint64_t)elem_size) % 16 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
 }
 
-bool gram_dma_eligible(int J, uint64_t L, int elem_size, const void* Y) {
+// Row segments: this kernel leaves out the blocks past J of a ragged last tile,
+// which the register-staged tile pairs multiply, but takes its chunks slab by
+// slab, so a last chunk that a short slab does not fill is work as well.
+// `gain` is the block products of the one over those of the other.  With
+// 16-byte loads FP64 and, on filled chunks, FP32 are the faster here whatever
+// the gain (FP32, 256 rows: 3.2 against 3.9 ms); with 4-byte loads, whose
+// issue the products no longer cover, and for BF16X6, whose pieces are made
+// again by every wave, the lines lie where the two measured the same.  Register-
+// staged against here, in ms, 400000 columns in slabs of L, J at gain:
+//   FP64   L =  67: 250 at 0.99 0.83 / 0.87, 336 at 1.16 1.62 / 1.48, 626 at 0.82 4.03 / 4.40
+//   FP32   L = 447: 200 at 2.11 0.45 / 0.35, 336 at 1.66 0.87 / 0.86, 626 at 1.17 2.13 / 2.83
+//          L = 161: 161 at 2.44 0.45 / 0.35, 200 at 1.77 0.45 / 0.41, 336 at 1.39 0.88 / 1.01
+//   BF16X6 L = 447: 161 at 2.91 0.40 / 0.33, 200 at 2.11 0.42 / 0.38, 336 at 1.66 0.85 / 0.96
+//          L =  67: 161 at 2.03 0.40 / 0.46; 16-byte loads, 512 at 1.21 4.24 / 4.60
+static bool rows_pay(int J, uint64_t L, int elem_size, bool w16, int prec) {
+  const int64_t KC = 128 / elem_size, nt = ceil_div(J, 128), nb = ceil_div(J, 16);
+  const double fill = (double)L / (double)(ceil_div((int64_t)L, KC) * KC);
+  const double gain = 64.0 * (double)(nt * (nt + 1)) / (double)(nb * (nb + 1)) * fill;
+  if (prec == 0) return w16 || gain >= (nt == 2 ? 1.2 : 1.0);
+  if (prec == 1) return gain >= 1.72 || (w16 && fill >= 0.95);
+  return gain >= 2.05;
+}
+
+bool gram_dma_eligible(int J, uint64_t L, int elem_size, const void* Y, int prec) {
   const uint64_t KC = 128 / elem_size;
-  return J > 128 && J <= (1 << 20) && (L == 1 || L >= 64 || L % KC == 0) &&
-         reinterpret_cast<uintptr_t>(Y) % elem_size == 0;
+  return J > 128 && J <= (1 << 20) && reinterpret_cast<uintptr_t>(Y) % elem_size == 0 &&
+         (L == 1 || ((L >= 64 || L % KC == 0) && rows_pay(J, L, elem_size, gram_dma_w16(J, L, elem_size, Y), prec)));
 }
 
 GramPlan plan_gram_dma(int J, uint64_t L, uint64_t K, int elem_size, int prec) {
@@ -552,7 +575,7 @@ GramPlan plan_gram_dma(int J, uint64_t L, uint64_t K, int elem_size, int prec) {
 template <typename T>
 hipError_t launch_gram_dma(const T* Y, int J, uint64_t L, uint64_t K, int prec, const GramPlan& p, double* part,
                            double* sq, double* S, double* norm2, hipStream_t stream, hipEvent_t after_main) {
-  if (!gram_dma_eligible(J, L, (int)sizeof(T), Y)) return hipErrorInvalidValue;
+  if (!gram_dma_eligible(J, L, (int)sizeof(T), Y, prec)) return hipErrorInvalidValue;
   if (prec != 0 && ((prec != 1 && prec != 3) || sizeof(T) != 4 || sq == nullptr)) return hipErrorInvalidValue;
   DmaParams g{};
   g.Y = reinterpret_cast<const char*>(Y);

@@ -37,11 +37,12 @@ struct GramPlan {
 
 // Gram for J > 128 with direct global-to-LDS staging (gram_dma.hip): float
 // or double input, unit stride (L = 1) or row segments (L >= 64 or L a
-// multiple of the chunk width 128 / sizeof(T)), any alignment of whole
-// elements.  Partial blocks in the tile-pair layout of
+// multiple of the chunk width 128 / sizeof(T), and the register-staged kernel
+// not the faster one), any alignment of whole elements; prec: 0 FP64, 1 FP32,
+// 3 BF16X6 products.  Partial blocks in the tile-pair layout of
 // launch_gram_pair_reduce; norm2 (may be null) receives the FP64 sum of
 // squares (trace(S) with FP64 products).
-bool gram_dma_eligible(int J, uint64_t L, int elem_size, const void* Y);
+bool gram_dma_eligible(int J, uint64_t L, int elem_size, const void* Y, int prec);
 // prec 0: FP64 products; prec 1: FP32 products, prec 3: BF16X6 products, both
 // of float input (sq: one double per item, p.sq_elems).  Other combinations
 // return hipErrorInvalidValue.
