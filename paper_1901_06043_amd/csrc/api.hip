@@ -1314,7 +1314,10 @@ tucker_status reconstruct_impl(const tucker_t* t, const tucker_op* ops, const in
       M[k] = t->U[k] + (op[k].kind == TUCKER_OP_RANGE ? op[k].begin : 0);
       msk[k] = 1;
       msj[k] = t->dims[k];
-      if (!f32p && tk::ttm_dma_wants_pack((int)t->ranks[k], 1, (int)K[k], 1, msj[k], 8, nullptr, M[k])) {
+      uint64_t cols = 1;  // at most: whatever the order of the products
+      for (int q = 0; q < N; ++q)
+        if (q != k) cols *= (uint64_t)std::max(K[q], t->ranks[q]);
+      if (!f32p && tk::ttm_dma_wants_pack((int)t->ranks[k], cols, (int)K[k], 1, msj[k], 8, nullptr, M[k])) {
         // odd mode size or begin
         if (optional_scratch(wbuf[k], sizeof(double) * K[k] * (t->ranks[k] + 1), stream) &&
             (st = pack_factor(M[k], msk[k], msj[k], K[k], t->ranks[k], wbuf[k].as<double>(), stream)))

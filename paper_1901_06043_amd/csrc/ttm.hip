@@ -704,8 +704,15 @@ template <typename TI, typename TO, typename CT>
 hipError_t launch_ttm_ct(const TI* Y, int J, uint64_t L, uint64_t cols, const double* M, int64_t msk, int64_t msj,
                          int K, TO* Z, hipStream_t stream) {
   // pairs of columns on both sides; past 32 rows the resident kernel's loads
-  // of several blocks are in flight anyway (33 -> 33 rows: 5.1 TB/s)
-  if (L > 1 && L % 2 == 0 && J <= 32 && K <= 64 && reinterpret_cast<uintptr_t>(Y) % (2 * sizeof(TI)) == 0 &&
+  // of several blocks are in flight anyway (33 -> 33 rows: 5.1 TB/s).  Shorter
+  // slabs leave partial lines to write (L = 2, 4 -> 27 rows: 0.12 ms for 2
+  // million columns in the resident kernel, 0.31 ms here; L = 64: 0.24 and
+  // 0.11 ms); with slabs that hold whole tiles of the resident kernel, many sums
+  // per lane cost more than its passes (L = 5000: 32 -> 50 rows 0.24 and 0.30 ms,
+  // 11 -> 50 the same, 11 -> 12 0.08 and 0.06 ms), as do many rows for few sums
+  // (32 -> 3 rows: 0.104 and 0.112 ms).
+  if (L >= 64 && L % 2 == 0 && J <= 32 && K <= 64 && J <= 8 * K && (L <= 96 || (K <= 50 && J * K <= 900)) &&
+      reinterpret_cast<uintptr_t>(Y) % (2 * sizeof(TI)) == 0 &&
       reinterpret_cast<uintptr_t>(Z) % (2 * sizeof(TO)) == 0) {
     launch_ttm_slab<TI, TO, CT>(Y, J, L, cols, M, msk, msj, K, Z, stream);
     return hipGetLastError();
