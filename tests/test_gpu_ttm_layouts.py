@@ -146,3 +146,20 @@ def test_ttm_without_scratch(tk):
         check(tk, [33, 51, 7], 0, 71, "rows", np.float32, np.float64)
     finally:
         assert tk.lib().tucker_set_allocator(None) == 0
+
+
+# past 1e9 flops the factor is laid out first where it is not in 16-byte units:
+# slabs and unit stride, every layout, and no memory for the copy
+@pytest.mark.parametrize("dims,n,K", [([66, 201, 700], 1, 71), ([201, 46200], 0, 71), ([65, 201, 711], 1, 71)])
+def test_ttm_factor_laid_out(tk, dims, n, K):
+    import ctypes
+    check(tk, dims, n, K, "columns", np.float64, np.float32)
+    check(tk, dims, n, K, "rows", np.float32, np.float64)
+    check(tk, dims, n, K, "strided", np.float64, np.float64)
+    alloc, free = (f[1] for f in tk._Allocator._fields_[:2])
+    none = tk._Allocator(alloc(lambda nbytes, ctx, stream: None), free(lambda p, ctx, stream: None), None)
+    assert tk.lib().tucker_set_allocator(ctypes.byref(none)) == 0
+    try:
+        check(tk, dims, n, K, "columns", np.float64, np.float64)
+    finally:
+        assert tk.lib().tucker_set_allocator(None) == 0
