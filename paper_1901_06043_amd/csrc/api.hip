@@ -263,21 +263,46 @@ struct TmpBuf {
   }
 };
 
-// Small pinned host staging area, one per thread: kernels write ranks, norms
-// and flags there, and the host reads them after an event or the stream.
-struct Pinned {
-  void* p = nullptr;
-  ~Pinned() {
-    if (p) (void)hipHostFree(p);
+// Small pinned host staging areas: kernels write ranks, norms and flags there,
+// and the host reads them after an event or the stream.  Every call takes one
+// for itself (an allocator callback may call the library in the middle of a
+// call) and gives it back on whichever way it returns, once nothing that it
+// enqueued can write there any more: a call that ends early waits for its
+// stream first.  A thread keeps a few for its next calls.
+constexpr size_t kHostBlockBytes = 4096;
+constexpr int kHostBlocksKept = 4;
+struct HostBlocks {
+  void* idle[kHostBlocksKept] = {nullptr};
+  int n = 0;
+  ~HostBlocks() {
+    while (n > 0) (void)hipHostFree(idle[--n]);
   }
 };
-thread_local Pinned g_pinned;
+thread_local HostBlocks g_host_blocks;
 
-tucker_status pinned(void** out) {
-  if (!g_pinned.p) HIP_TRY(hipHostMalloc(&g_pinned.p, 4096, hipHostMallocCoherent));
-  *out = g_pinned.p;
-  return TUCKER_OK;
-}
+struct HostBlock {
+  void* p = nullptr;
+  hipStream_t s = nullptr;
+  bool pending = false;  // kernels that write to the block may not have run yet on s
+  HostBlock() = default;
+  HostBlock(const HostBlock&) = delete;
+  HostBlock& operator=(const HostBlock&) = delete;
+  ~HostBlock() {
+    if (!p) return;
+    if (pending && hipStreamSynchronize(s) != hipSuccess) return;  // (never handed out again)
+    HostBlocks& k = g_host_blocks;
+    if (k.n < kHostBlocksKept) k.idle[k.n++] = p;
+    else (void)hipHostFree(p);
+  }
+  hipError_t take(hipStream_t st) {
+    s = st;
+    if (g_host_blocks.n > 0) {
+      p = g_host_blocks.idle[--g_host_blocks.n];
+      return hipSuccess;
+    }
+    return hipHostMalloc(&p, kHostBlockBytes, hipHostMallocCoherent | hipHostMallocPortable);
+  }
+};
 
 tucker_status validate_dims(const int64_t* dims, int N) {
   if (!dims) return fail(TUCKER_EINVAL, "dims is NULL");
@@ -739,15 +764,15 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
   // with given ranks in FP64 nothing depends on a read-back: one synchronisation at the end
   const bool async = fixed_ranks && !reduced;
 
-  void* hp = nullptr;
-  if ((st = pinned(&hp))) return st;
+  HostBlock hb;
+  HIP_TRY(hb.take(stream));
   struct HostScalars {
     int64_t R[TUCKER_MAX_MODES];
     double disc[TUCKER_MAX_MODES];
     double nx2, flag;
   };
-  static_assert(sizeof(HostScalars) <= 4096, "fits the pinned staging area");
-  HostScalars* h = static_cast<HostScalars*>(hp);
+  static_assert(sizeof(HostScalars) <= kHostBlockBytes, "fits the pinned staging area");
+  HostScalars* h = static_cast<HostScalars*>(hb.p);
 
   Events evs;
   HIP_TRY(evs.create(7 * N));  // 5 per step, then 2 per deferred product
@@ -842,6 +867,7 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
         eh.dflag = d_flag + step;
         eh.flag = &h->flag;
       }
+      hb.pending = true;
       HIP_TRY(tk::launch_eig_values(Sbuf.as<double>(), (int)J, thr_mul, fixed_ranks ? nullptr : d_nx2, fixed, w,
                                     t->lam[n], t->dranks + n, d_disc + n, stream, eh));
       if (!async) HIP_TRY(hipEventRecord(rank_ready, stream));
@@ -849,6 +875,7 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
       HIP_TRY(hipEventRecord(ev[2], stream));
       if (async) break;
       HIP_TRY(hipEventSynchronize(rank_ready));
+      hb.pending = false;
       if (pp == TUCKER_GRAM_FP64 || h->flag == 0.0) break;
       if (pass == 0) t->scaled[n] = 1;
       else t->prec_used[n] = TUCKER_GRAM_FP64;
@@ -980,6 +1007,7 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
   t->owned.push_back(ybuf.p);
   ybuf.p = nullptr;
   HIP_TRY(hipStreamSynchronize(stream));
+  hb.pending = false;
   std::memcpy(t->disc, h->disc, sizeof(double) * N);
   if (async) {
     const double nx2 = h->nx2;
@@ -2283,11 +2311,10 @@ tucker_status tucker_batch_item(tucker_batch* b, int i, tucker_t** out) {
   // back the whole batch and copying array by array cost 16 copies and 8
   // blocks per item: 170 us, 17 of the 19 ms that a batch of 96 tensors and
   // its items took.
-  void* hp = nullptr;
-  tucker_status st;
-  if ((st = pinned(&hp))) return st;
-  static_assert(sizeof(ItemScalars) <= 4096, "fits the pinned staging area");
-  ItemScalars* h = static_cast<ItemScalars*>(hp);
+  HostBlock hb;
+  HIP_TRY(hb.take(s));
+  static_assert(sizeof(ItemScalars) <= kHostBlockBytes, "fits the pinned staging area");
+  ItemScalars* h = static_cast<ItemScalars*>(hb.p);
   ItemSources src{};
   for (int k = 0; k < N; ++k) {
     src.R[k] = b->R[k];
@@ -2296,9 +2323,11 @@ tucker_status tucker_batch_item(tucker_batch* b, int i, tucker_t** out) {
   src.nx2 = b->nx2;
   src.N = N;
   src.t = i;
+  hb.pending = true;
   hipLaunchKernelGGL(batch_item_scalars_kernel, dim3(1), dim3(64), 0, s, src, h);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(s));
+  hb.pending = false;
   HandleGuard g(new tucker_t);
   tucker_t* t = g.t;
   t->N = N;
