@@ -410,8 +410,8 @@ tucker_status tucker_sthosvd_batched(int count, const void* const* data, tucker_
                                      const int64_t* dims, int N, double eps, const int* mode_order,
                                      tucker_gram_prec prec, hipStream_t stream, tucker_batch** out);
 /* Results of the last run; each call synchronises the stream given to the
- * last tucker_batch_run (after replaying a captured run on another stream,
- * synchronise that stream first).  host out[count*N] ranks; host out[count]
+ * last tucker_batch_run and the null stream (after replaying a captured run on
+ * another stream, synchronise that stream first).  host out[count*N] ranks; host out[count]
  * ||X_t||^2. */
 tucker_status tucker_batch_ranks(tucker_batch* b, int64_t* ranks_out);
 tucker_status tucker_batch_norm2(tucker_batch* b, double* norm2_out);

@@ -2311,8 +2311,11 @@ tucker_status tucker_batch_item(tucker_batch* b, int i, tucker_t** out) {
   // back the whole batch and copying array by array cost 16 copies and 8
   // blocks per item: 170 us, 17 of the 19 ms that a batch of 96 tensors and
   // its items took.
+  // The kernel runs on the null stream, where the read-backs of the whole batch
+  // are made: behind a captured run that was replayed there (the run's own
+  // stream, the captured one, knows nothing of a replay on another).
   HostBlock hb;
-  HIP_TRY(hb.take(s));
+  HIP_TRY(hb.take(nullptr));
   static_assert(sizeof(ItemScalars) <= kHostBlockBytes, "fits the pinned staging area");
   ItemScalars* h = static_cast<ItemScalars*>(hb.p);
   ItemSources src{};
@@ -2323,10 +2326,11 @@ tucker_status tucker_batch_item(tucker_batch* b, int i, tucker_t** out) {
   src.nx2 = b->nx2;
   src.N = N;
   src.t = i;
+  if (s) HIP_TRY(hipStreamSynchronize(s));
   hb.pending = true;
-  hipLaunchKernelGGL(batch_item_scalars_kernel, dim3(1), dim3(64), 0, s, src, h);
+  hipLaunchKernelGGL(batch_item_scalars_kernel, dim3(1), dim3(64), 0, nullptr, src, h);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(hipStreamSynchronize(nullptr));
   hb.pending = false;
   HandleGuard g(new tucker_t);
   tucker_t* t = g.t;

@@ -117,3 +117,34 @@ def test_allocator_that_calls_the_library(tk, given):
     with HookedAllocator(tk, hook):
         assert run() == alone
     assert len(inner) > 8 and all(v == inner[0] for v in inner)
+
+
+def test_item_after_replay_on_the_null_stream(tk):
+    """A captured run replayed on the null stream behind other work: an item
+    taken right after it is the replay's, as the ranks of the whole batch are."""
+    x, other = tensor(5, [30, 40, 50]), tensor(6, [30, 40, 50], 2.0)
+    other[:, :, 10:] *= 1e-6
+    ref = tk.Batch([other.clone()], 1e-2)
+    ref.run()
+    want, core = told(ref.item(0)), ref.item(0).core.clone()
+    b = tk.Batch([x], 1e-2)
+    b.run()
+    assert told(b.item(0)) != want
+    busy = torch.randn(8192, 8192, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        b.run()
+    first = x.clone()
+    for src in (other, first, other):
+        for _ in range(10):
+            busy @ busy
+        x.copy_(src)
+        g.replay()
+        t = b.item(0)
+        if src is other:
+            assert told(t) == want
+            assert torch.equal(t.core, core)
+        else:
+            assert told(t) != want
+        assert b.ranks()[0] == t.ranks
