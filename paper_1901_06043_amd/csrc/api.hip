@@ -1342,9 +1342,12 @@ tucker_status reconstruct_impl(const tucker_t* t, const tucker_op* ops, const in
       M[k] = t->U[k] + (op[k].kind == TUCKER_OP_RANGE ? op[k].begin : 0);
       msk[k] = 1;
       msj[k] = t->dims[k];
-      uint64_t cols = 1;  // at most: whatever the order of the products
-      for (int q = 0; q < N; ++q)
-        if (q != k) cols *= (uint64_t)std::max(K[q], t->ranks[q]);
+      uint64_t cols = 1;  // of this mode's product in the order taken
+      bool done = true;
+      for (int q = 0; q < N; ++q) {
+        if (ord[q] == k) done = false;
+        else cols *= (uint64_t)(done ? K[ord[q]] : t->ranks[ord[q]]);
+      }
       if (!f32p && tk::ttm_dma_wants_pack((int)t->ranks[k], cols, (int)K[k], 1, msj[k], 8, nullptr, M[k])) {
         // odd mode size or begin
         if (optional_scratch(wbuf[k], sizeof(double) * K[k] * (t->ranks[k] + 1), stream) &&

@@ -96,7 +96,8 @@ __global__ void sum_fixed_kernel(const double* __restrict__ x, int64_t n, double
 // FP64 mode product for more than 64 output rows with direct global-to-LDS
 // staging (ttm_dma.hip): M with contiguous rows (msj = 1) or, for double Y,
 // columns (msk = 1) and even stride, 16-byte aligned; any Y and output of
-// float or double.  launch_ttm uses it when eligible.
+// float or double, but float Y of more than 32 rows only from the number of
+// tiles on where it is the faster.  launch_ttm uses it when eligible.
 bool ttm_dma_eligible(int J, uint64_t L, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
                       const void* M);
 // True where only the layout of M stands in the way: a copy P (K x ld, rows

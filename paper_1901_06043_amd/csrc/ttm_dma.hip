@@ -459,20 +459,38 @@ static bool ttm_dma_m16(int J, int K, int64_t msk, int64_t msj, int ysize, const
   return ttm_dma_mrow(J, msk, msj) || (ysize == 8 && msk == 1 && msj % 2 == 0 && msj >= K);
 }
 
+// Up to 128 tiles (of 128 x 128) leave half of the CUs without one, and a call
+// takes as long as one tile's chain of chunks, in which the register-staged
+// kernel of smaller tiles is the faster for float Y, whose values it converts
+// once and not at every operand read, from three chunks on.  That kernel
+// against this one, in us, rows J -> K of C columns in slabs of 50:
+//   626 -> 468: C = 2000 (64 tiles) 64 / 89, 4000 (128) 73 / 91, 8000 (252) 112 / 93
+//   336 -> 200: C = 2000 (32) 38 / 44, 8000 (126) 42 / 46, 16000 (250) 70 / 48
+//   (slabs of 25) 32 -> 200: C = 1000 (16) 9.5 / 8.8; 16 -> 200: 9.6 / 7.1
+// Doubles take this kernel whatever their number.
+constexpr int64_t kTDFew = 128;
+static int64_t ttm_dma_tiles(int K, uint64_t cols) {
+  return ceil_div(ceil_div(K, 16), 8) * ceil_div((int64_t)cols, 128);
+}
+
 bool ttm_dma_eligible(int J, uint64_t L, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
                       const void* M) {
   (void)L;
   if (K <= 64 || J < 16 || cols == 0) return false;
+  if (ysize == 4 && J > 2 * kJC && ttm_dma_tiles(K, cols) <= kTDFew) return false;
   return ttm_dma_m16(J, K, msk, msj, ysize, M) && reinterpret_cast<uintptr_t>(Y) % ysize == 0;
 }
 
 bool ttm_dma_wants_pack(int J, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
                         const void* M) {
   if (K <= 64 || J < 16 || cols == 0 || reinterpret_cast<uintptr_t>(Y) % ysize) return false;
-  // the launch that lays M out takes 6 us: 50 -> 129 rows of 2000 columns
-  // (2.6e7 flops) 14 us without it and 22 us with it, 50 -> 65 rows of 200000
-  // columns (1.3e9) faster with it
-  if (2.0 * K * J * (double)cols < 1e9) return false;
+  // The launch that lays M out takes 6 us, and moves M twice more: 50 -> 129
+  // rows of 2000 columns (2.6e7 flops) 14 us without it and 22 us with it, 50 ->
+  // 65 rows of 200000 columns (1.3e9) faster with it; 201 -> 20001 rows of 500
+  // columns 126 and 112 us, of 1000 242 and 175 us, but 50 -> 20001 rows of 500
+  // slower.  With few tiles it gains nothing even then: 201 -> 201 rows of 8000
+  // columns (126 tiles) 31 and 34 us, of 16000 (250) 50 and 35 us.
+  if (2.0 * K * J * (double)cols < 1e9 || cols < 1000 || ttm_dma_tiles(K, cols) <= kTDFew) return false;
   return !ttm_dma_m16(J, K, msk, msj, ysize, M);
 }
 

@@ -163,3 +163,16 @@ def test_ttm_factor_laid_out(tk, dims, n, K):
         check(tk, dims, n, K, "columns", np.float64, np.float64)
     finally:
         assert tk.lib().tucker_set_allocator(None) == 0
+
+
+# around the number of tiles (128), of rows (two chunks) and of columns (1000)
+# at which float tensors and laid-out factors go to the direct-load kernel
+@pytest.mark.parametrize("dims,n,K", [
+    ([128, 32, 128], 1, 65), ([128, 33, 128], 1, 65), ([128, 33, 129], 1, 65), ([63, 34, 128], 1, 200),
+    ([63, 34, 131], 1, 200), ([251, 999], 0, 2049), ([251, 1000], 0, 2049), ([251, 7937], 0, 257),
+])
+def test_ttm_few_tiles(tk, dims, n, K):
+    for zdt in (np.float64, np.float32):
+        check(tk, dims, n, K, "rows", np.float32, zdt)
+    check(tk, dims, n, K, "columns", np.float32, np.float64)
+    check(tk, dims, n, K, "columns", np.float64, np.float64)
