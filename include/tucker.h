@@ -472,7 +472,11 @@ tucker_status tucker_eig_truncate_noalloc(const double* S, int64_t J, double thr
  * matrix with element (k,j) at M[k*msk + j*msj]; Z has the sizes of Y with
  * mode n replaced by K, in `zdtype`.  Y in `ydtype`.  fp32_products != 0
  * rounds M and Y to FP32 and uses FP32 MFMA products (FP32 accumulation);
- * otherwise products and accumulation are FP64. */
+ * otherwise products and accumulation are FP64.  Only enqueues kernels: large
+ * FP64 products whose M is not in 16-byte units are faster with 8 K (J_n + 1)
+ * bytes of scratch for an aligned copy, which is taken from the library's pool
+ * (or the caller's allocator) if it is at hand without freeing or waiting for
+ * anything, and not while `stream` is being captured. */
 tucker_status tucker_ttm(const void* Y, tucker_dtype ydtype, const int64_t* dims, int N, int n,
                          const double* M, int64_t K, int64_t msk, int64_t msj, void* Z,
                          tucker_dtype zdtype, int fp32_products, hipStream_t stream);

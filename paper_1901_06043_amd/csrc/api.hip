@@ -91,41 +91,48 @@ size_t round_bytes(size_t b) {
   return (b + g - 1) / g * g;
 }
 
+// A block from the caller's allocator, where one is set (else `set` is false).
+hipError_t ext_alloc(void** out, size_t bytes, hipStream_t s, bool& set) {
+  tucker_allocator ext{};
+  {
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    set = g_ext_set;
+    ext = g_ext;
+  }
+  if (!set) return hipSuccess;
+  void* p = ext.alloc(bytes, ext.ctx, s);
+  if (!p) return hipErrorOutOfMemory;
+  *out = p;
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  g_cache_live.push_back({p, bytes, true, ext});
+  return hipSuccess;
+}
+
+// The smallest idle block of this stream that holds `bytes` without wasting much.
+bool cached_alloc(void** out, size_t bytes, hipStream_t s, int dev) {
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  int best = -1;
+  for (int i = 0; i < (int)g_cache_free.size(); ++i) {
+    const CachedBlock& b = g_cache_free[i];
+    if (b.dev != dev || b.stream != s || b.bytes < bytes || b.bytes > 2 * bytes + (size_t(4) << 20)) continue;
+    if (best < 0 || b.bytes < g_cache_free[best].bytes) best = i;
+  }
+  if (best < 0) return false;
+  *out = g_cache_free[best].p;
+  g_cache_live.push_back({*out, g_cache_free[best].bytes, false, {}});
+  g_cache_free.erase(g_cache_free.begin() + best);
+  return true;
+}
+
 hipError_t dev_alloc(void** out, size_t bytes, hipStream_t s) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   bytes = round_bytes(bytes);
-  tucker_allocator ext{};
-  bool use_ext = false;
-  {
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    use_ext = g_ext_set;
-    ext = g_ext;
-  }
-  if (use_ext) {
-    void* p = ext.alloc(bytes, ext.ctx, s);
-    if (!p) return hipErrorOutOfMemory;
-    *out = p;
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    g_cache_live.push_back({p, bytes, true, ext});
-    return hipSuccess;
-  }
-  {
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    int best = -1;
-    for (int i = 0; i < (int)g_cache_free.size(); ++i) {
-      const CachedBlock& b = g_cache_free[i];
-      if (b.dev != dev || b.stream != s || b.bytes < bytes || b.bytes > 2 * bytes + (size_t(4) << 20)) continue;
-      if (best < 0 || b.bytes < g_cache_free[best].bytes) best = i;
-    }
-    if (best >= 0) {
-      *out = g_cache_free[best].p;
-      g_cache_live.push_back({*out, g_cache_free[best].bytes, false, {}});
-      g_cache_free.erase(g_cache_free.begin() + best);
-      return hipSuccess;
-    }
-  }
+  bool ext = false;
+  e = ext_alloc(out, bytes, s, ext);
+  if (ext) return e;
+  if (cached_alloc(out, bytes, s, dev)) return hipSuccess;
   // Make room first: when the device has less than the request (plus 1 GiB)
   // free, an idle block of this stream of any larger size is reused, else
   // idle cached blocks of this device go back to HIP, largest first, until the
@@ -197,6 +204,41 @@ hipError_t dev_alloc(void** out, size_t bytes, hipStream_t s) {
   return e;
 }
 
+// A block that the caller can do without, got without disturbing anything: an
+// idle block of this stream, or fresh memory while plenty is free.  No block
+// is freed for it, no work is waited for, and a stream that is being captured
+// (by any thread) stays valid: its own gets none, and hipMalloc for another one
+// runs in the relaxed capture mode.
+bool dev_alloc_quiet(void** out, size_t bytes, hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  int dev = 0;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (cap != hipStreamCaptureStatusNone) return false;
+  bytes = round_bytes(bytes);
+  bool ext = false;
+  const hipError_t e = ext_alloc(out, bytes, s, ext);
+  if (ext) return e == hipSuccess;
+  if (cached_alloc(out, bytes, s, dev)) return true;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  if (ok) {
+    size_t fr = 0, tot = 0;
+    ok = hipMemGetInfo(&fr, &tot) == hipSuccess && fr >= bytes + (size_t(1) << 30) &&
+         hipMalloc(out, bytes) == hipSuccess;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  if (!ok) {
+    (void)hipGetLastError();
+    return false;
+  }
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  g_cache_live.push_back({*out, bytes, false, {}});
+  return true;
+}
+
 // Bytes the built-in pool can hand out on this device without a failed
 // allocation: free device memory plus idle cached blocks.  SIZE_MAX when a
 // caller-supplied allocator is set (its capacity is not known here).
@@ -256,6 +298,12 @@ struct TmpBuf {
     release();
     s = st;
     return dev_alloc(&p, bytes, st);
+  }
+  // Scratch that only makes a call faster.
+  bool alloc_quiet(size_t bytes, hipStream_t st) {
+    release();
+    s = st;
+    return dev_alloc_quiet(&p, bytes, st);
   }
   template <typename T>
   T* as() const {
@@ -427,19 +475,10 @@ tucker_status pack_factor(const double*& M, int64_t& msk, int64_t& msj, int64_t 
   return TUCKER_OK;
 }
 
-// Scratch that only makes a call faster: none while the stream is being captured
-// (an allocation would end the capture) or where the allocation fails.
-bool optional_scratch(TmpBuf& b, size_t bytes, hipStream_t s) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
-  if (b.alloc(bytes, s) == hipSuccess) return true;
-  (void)hipGetLastError();
-  return false;
-}
-
 // `scratch` (may be null): K * (J + 1) doubles for an aligned copy of M, free
-// until the work enqueued here has run; null allocates the copy where one is
-// needed (without it the kernel that reads M as it is takes the product).
+// until the work enqueued here has run; null takes memory for the copy where
+// one is wanted and memory is at hand (without it the kernel that reads M as it
+// is takes the product).
 tucker_status run_ttm(const void* Y, tucker_dtype yd, const int64_t* dims, int N, int n, const double* M,
                       int64_t K, int64_t msk, int64_t msj, void* Z, tucker_dtype zd, bool f32p, hipStream_t s,
                       double* scratch = nullptr) {
@@ -451,7 +490,7 @@ tucker_status run_ttm(const void* Y, tucker_dtype yd, const int64_t* dims, int N
     return fail(TUCKER_EUNSUPPORTED, "TTM of mode %d too large for 32-bit column indexing", n);
   TmpBuf packed;
   if (!f32p && tk::ttm_dma_wants_pack((int)J, (uint64_t)cols, (int)K, msk, msj, (int)dtype_size(yd), Y, M)) {
-    if (!scratch && optional_scratch(packed, sizeof(double) * K * (J + 1), s)) scratch = packed.as<double>();
+    if (!scratch && packed.alloc_quiet(sizeof(double) * K * (J + 1), s)) scratch = packed.as<double>();
     tucker_status st;
     if (scratch && (st = pack_factor(M, msk, msj, K, J, scratch, s))) return st;
   }
@@ -1350,7 +1389,7 @@ tucker_status reconstruct_impl(const tucker_t* t, const tucker_op* ops, const in
       }
       if (!f32p && tk::ttm_dma_wants_pack((int)t->ranks[k], cols, (int)K[k], 1, msj[k], 8, nullptr, M[k])) {
         // odd mode size or begin
-        if (optional_scratch(wbuf[k], sizeof(double) * K[k] * (t->ranks[k] + 1), stream) &&
+        if (wbuf[k].alloc_quiet(sizeof(double) * K[k] * (t->ranks[k] + 1), stream) &&
             (st = pack_factor(M[k], msk[k], msj[k], K[k], t->ranks[k], wbuf[k].as<double>(), stream)))
           return st;
       }

@@ -176,3 +176,65 @@ def test_ttm_few_tiles(tk, dims, n, K):
         check(tk, dims, n, K, "rows", np.float32, zdt)
     check(tk, dims, n, K, "columns", np.float32, np.float64)
     check(tk, dims, n, K, "columns", np.float64, np.float64)
+
+
+def raw_ttm(tk, y, M, z, stream):
+    """Mode 0 of y (cols x J) into z without an allocation on the way."""
+    st = tk.lib().tucker_ttm(y.data_ptr(), tk.F64, tk._i64([y.shape[1], y.shape[0]]), 2, 0, M.data_ptr(), M.shape[0],
+                             M.stride(0), M.stride(1), z.data_ptr(), tk.F64, 0, int(stream.cuda_stream))
+    assert st == 0
+
+
+def laid_out_operands():
+    g = torch.Generator(device="cuda").manual_seed(4)
+    y = torch.randn(40000, 201, dtype=torch.float64, device="cuda", generator=g)
+    M = torch.randn(71, 201, dtype=torch.float64, device="cuda", generator=g)
+    z = torch.zeros(40000, 71, dtype=torch.float64, device="cuda")
+    return y, M, z, y @ M.t(), 1e-12 * (y.abs() @ M.abs().t())
+
+
+def test_ttm_beside_a_capture(tk):
+    """A product that wants scratch, on a stream that has none, while another
+    stream is being captured: it runs, and the capture stays valid."""
+    y, M, z, ref, tol = laid_out_operands()
+    x = torch.ones(1000, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = x * 2.0
+        raw_ttm(tk, y, M, z, side)
+        out = out + 1.0
+    side.synchronize()
+    assert bool(((z - ref).abs() <= tol).all())
+    for v in (1.0, 5.0):
+        x.fill_(v)
+        g.replay()
+        torch.cuda.synchronize()
+        assert bool((out == 2.0 * v + 1.0).all())
+
+
+def test_ttm_on_a_full_device_waits_for_nothing(tk):
+    """Scratch that is not at hand is done without: no idle block is given back
+    and other streams are not waited for."""
+    y, M, z, ref, tol = laid_out_operands()
+    busy = torch.randn(8192, 8192, device="cuda")
+    busy @ busy
+    tk.gram(y, 0)  # leaves idle blocks in the pool
+    sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    out = torch.empty_like(busy)
+    filler = torch.empty(torch.cuda.mem_get_info()[0] - (1 << 29), dtype=torch.uint8, device="cuda")
+    try:
+        with torch.cuda.stream(sa):
+            for _ in range(20):
+                torch.mm(busy, busy, out=out)
+        raw_ttm(tk, y, M, z, sb)
+        assert not sa.query()
+        sb.synchronize()
+        assert bool(((z - ref).abs() <= tol).all())
+    finally:
+        torch.cuda.synchronize()
+        del filler
+        torch.cuda.empty_cache()
