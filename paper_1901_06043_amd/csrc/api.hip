@@ -437,15 +437,22 @@ tucker_status run_gram(const void* Y, tucker_dtype dt, const int64_t* dims, int 
     // larger modes, every form but BF16X3: tile pairs staged by direct
     // global-to-LDS loads
     tk::GramPlan p = tk::plan_gram_dma((int)J, (uint64_t)L, (uint64_t)K, es, dprec);
-    HIP_TRY(part.alloc(sizeof(double) * p.part_elems, s));
-    if (p.sq_elems) HIP_TRY(sq.alloc(sizeof(double) * p.sq_elems, s));
-    if (dt == TUCKER_F64)
-      HIP_TRY(tk::launch_gram_dma(static_cast<const double*>(Y), (int)J, L, K, dprec, p, part.as<double>(),
-                                  sq.as<double>(), S, norm2, s, after_main));
-    else
-      HIP_TRY(tk::launch_gram_dma(static_cast<const float*>(Y), (int)J, L, K, dprec, p, part.as<double>(),
-                                  sq.as<double>(), S, norm2, s, after_main));
-    return TUCKER_OK;
+    hipError_t e = part.alloc(sizeof(double) * p.part_elems, s);
+    if (e == hipSuccess && p.sq_elems) e = sq.alloc(sizeof(double) * p.sq_elems, s);
+    if (e == hipSuccess) {
+      if (dt == TUCKER_F64)
+        HIP_TRY(tk::launch_gram_dma(static_cast<const double*>(Y), (int)J, L, K, dprec, p, part.as<double>(),
+                                    sq.as<double>(), S, norm2, s, after_main));
+      else
+        HIP_TRY(tk::launch_gram_dma(static_cast<const float*>(Y), (int)J, L, K, dprec, p, part.as<double>(),
+                                    sq.as<double>(), S, norm2, s, after_main));
+      return TUCKER_OK;
+    }
+    // no room for its partials (up to 1 GB): the register-staged kernel's are a
+    // sixteenth
+    if (e != hipErrorOutOfMemory) HIP_TRY(e);
+    (void)hipGetLastError();
+    part.release();
   }
   tk::GramPlan p = tk::plan_gram_mp((int)J, (uint64_t)K, (int)prec);
   HIP_TRY(part.alloc(sizeof(double) * p.part_elems, s));
@@ -643,8 +650,9 @@ tucker_gram_prec resolve_auto(tucker_dtype dtype, int N, double eps, bool fixed)
   return TUCKER_GRAM_FP64;
 }
 
-// Scratch of one Gram of mode n (split-K partials and sums of squares).
-int64_t gram_scratch_doubles(const int64_t* dims, int N, int n, tucker_gram_prec prec) {
+// Scratch of one Gram of mode n (split-K partials and sums of squares): of the
+// kernel that it takes, or the least that it can do with.
+int64_t gram_scratch_doubles(const int64_t* dims, int N, int n, tucker_gram_prec prec, bool least) {
   int64_t L, Rt;
   left_right(dims, N, n, L, Rt);
   const int64_t J = dims[n], K = L * Rt;
@@ -654,7 +662,7 @@ int64_t gram_scratch_doubles(const int64_t* dims, int N, int n, tucker_gram_prec
   else p = tk::plan_gram_mp((int)J, (uint64_t)K, (int)prec);
   int64_t need = p.part_elems + p.sq_elems;
   const int dprec = dma_gram_prec(prec);
-  if (dprec >= 0 && J > (dprec == 0 ? tk::kTriMaxJ : tk::kStreamMaxJ)) {
+  if (!least && dprec >= 0 && J > (dprec == 0 ? tk::kTriMaxJ : tk::kStreamMaxJ)) {
     // the tile-pair kernel with direct LDS loads (FP64: either input type;
     // reduced forms: float input)
     for (int es : {4, 8}) {
@@ -692,9 +700,10 @@ int64_t working_rank(const int64_t* cur, int N, const int* order, int step, int6
 // scalars, the Gram and eigensolver workspaces, and per step the current and
 // next working tensors plus that step's Gram scratch (and, for the reduced
 // forms, what the per-slice scaled pass needs).  `ranks` = NULL takes R_n =
-// J_n at every step (an upper bound when the ranks are not known).
+// J_n at every step (an upper bound when the ranks are not known).  `least`:
+// with the least Gram scratch, below which the compression is not tried.
 size_t predict_bytes(tucker_dtype dtype, const int64_t* dims, int N, const int64_t* ranks, const int* order,
-                     tucker_gram_prec prec) {
+                     tucker_gram_prec prec, bool least = false) {
   const bool reduced = (prec != TUCKER_GRAM_FP64);
   const size_t wsz = reduced ? 4 : 8;
   int64_t maxJ = 0;
@@ -718,7 +727,7 @@ size_t predict_bytes(tucker_dtype dtype, const int64_t* dims, int N, const int64
     padded = padded || (R != R0);
     const size_t ycur = (s == 0) ? 0 : round_bytes(wsz * total);
     const size_t ynext = round_bytes(wsz * (total / J * R));
-    size_t gram = round_bytes(sizeof(double) * gram_scratch_doubles(cur, N, n, prec));
+    size_t gram = round_bytes(sizeof(double) * gram_scratch_doubles(cur, N, n, prec, least));
     if (reduced) {
       int64_t L, Rt;
       left_right(cur, N, n, L, Rt);
@@ -780,8 +789,8 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
   {
     int64_t first[TUCKER_MAX_MODES];
     for (int k = 0; k < N; ++k) first[k] = (k == order[0]) ? dims[k] : 1;
-    const size_t need = fixed_ranks ? predict_bytes(dtype, dims, N, fixed_ranks, order, prec)
-                                    : predict_bytes(dtype, dims, N, first, order, prec);
+    const size_t need = fixed_ranks ? predict_bytes(dtype, dims, N, fixed_ranks, order, prec, true)
+                                    : predict_bytes(dtype, dims, N, first, order, prec, true);
     if ((st = fits(need, "the compression"))) return st;
   }
 

@@ -123,3 +123,39 @@ def test_batched_range_handling_and_status(tk, orc):
     assert b2.status() == [0, 0, 0, 0]
     b.free()
     b2.free()
+
+
+# unaligned columns (FP64) and row segments (FP64, FP32): tile pairs whose
+# partial sums are 1 GB where there is room
+@pytest.mark.parametrize("dims,order,prec", [
+    ([67, 300, 105, 100], [1, 0, 2, 3], "fp64"), ([301, 67, 105, 100], [0, 1, 2, 3], "fp64"),
+    ([447, 200, 50, 100], [1, 0, 2, 3], "fp32"),
+])
+def test_gram_with_little_room(tk, dims, order, prec):
+    """A compression that does without the large partial sums is neither
+    refused nor failed, and gives the same result to rounding."""
+    ranks = [3, 4, 2, 2]
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn(list(reversed(dims)), dtype=torch.float32, device="cuda", generator=g)
+    x += 3.0  # a leading component well above the noise
+    ref = tk.sthosvd_ranks(x, ranks, mode_order=order, prec=prec)
+    tk.empty_cache()
+    torch.cuda.empty_cache()
+    spare = 600 << 20
+    if prec != "fp64":  # the scaled copy of the range guard is part of the prediction
+        spare += x.numel() * 4
+    need = tk.sthosvd_memory(dims, tk.F32, ranks=ranks, mode_order=order, prec=prec)
+    assert need > spare
+    # (the free memory that is reported drops by less than a large allocation)
+    filler = [torch.empty(torch.cuda.mem_get_info()[0] - spare - (2 << 30), dtype=torch.uint8, device="cuda")]
+    filler.append(torch.empty(torch.cuda.mem_get_info()[0] - spare, dtype=torch.uint8, device="cuda"))
+    try:
+        assert torch.cuda.mem_get_info()[0] < need
+        t = tk.sthosvd_ranks(x, ranks, mode_order=order, prec=prec)
+    finally:
+        del filler
+        torch.cuda.empty_cache()
+    rtol = 1e-12 if prec == "fp64" else 1e-6
+    assert t.ranks == ref.ranks
+    assert abs(t.norm2 - ref.norm2) <= 1e-12 * ref.norm2
+    np.testing.assert_allclose(t.discarded, ref.discarded, rtol=rtol, atol=rtol * ref.norm2)
