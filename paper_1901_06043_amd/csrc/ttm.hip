@@ -576,21 +576,26 @@ __global__ __launch_bounds__(64 * kResWaves) void ttm_resident_kernel(const TI* 
   }
 }
 
-// Small product on slabs (L even, J <= 32, K <= 64): bound by reading Y and
-// writing Z, with a few MFMA steps per column.  A lane owns two neighbouring
-// columns of each row, so that a row of a wave's tile is one 128- or 256-byte
-// piece on both sides, both MFMA column groups share each factor operand, and
-// the next tile's loads are in flight during the products and stores of the
-// current one (two register sets, the loop unrolled by two so that no set is
-// moved).  MFMA step s of block jb takes reduction rows 16 jb + 4 s + q; steps
-// of padding rows only are left out.  Stores are nontemporal (9% less time on
-// the 36.9 GB output below, no loss on outputs that are read again at once).
-// The resident kernel below takes one 16-column group per wave, loads it and
+// Small product on slabs (L even; the shapes for which it is taken are at its
+// dispatch): bound by reading Y and writing Z, with a few MFMA steps per
+// column.  A lane owns two neighbouring columns of each row, so that a row of a
+// wave's tile is one 128- or 256-byte piece on both sides, both MFMA column
+// groups share each factor operand, and the next tile's loads are in flight
+// during the products and stores of the current one (two register sets, the
+// loop unrolled by two so that no set is moved).  The factor is in LDS; the
+// output rows are formed 16 at a time, and MFMA step s of block jb takes
+// reduction rows 16 jb + 4 s + q; steps of padding rows only are left out.
+// NT: nontemporal stores, 10 to 40% less time where every row of Z is whole
+// 64-byte pieces (2 million columns of doubles, L = 200: 12 -> 50 rows 241 us
+// with ordinary stores, 175 us with these), and several times more where
+// neighbouring tiles share pieces (floats, L = 66: 4 -> 27 rows 54 and 174 us),
+// which ordinary stores leave to L2 to put together.
+// The resident kernel above takes one 16-column group per wave, loads it and
 // waits: 12 -> 50 rows of 256x256x256x11x12, 36.9 GB of float output, took
 // 22.7 ms from doubles (FP64 products) and 20.0 ms from floats (FP32), and
 // takes 11.0 ms (5.0 TB/s) and 11.5 ms here.  Four columns per lane for
 // floats measured the same.
-template <typename TI, typename TO, typename CT, int RB, int NJ>
+template <typename TI, typename TO, typename CT, int RB, int NJ, bool NT>
 __global__ __launch_bounds__(256, 2) void ttm_slab_kernel(const TI* __restrict__ Y, int J, uint32_t L, uint32_t cols,
                                                           const double* __restrict__ M, int64_t msk, int64_t msj,
                                                           int K, TO* __restrict__ Z, int64_t nct) {
@@ -661,7 +666,11 @@ __global__ __launch_bounds__(256, 2) void ttm_slab_kernel(const TI* __restrict__
         ovec o;
 #pragma unroll
         for (int u = 0; u < V; ++u) o[u] = static_cast<TO>(acc[u][v]);
-        if (cok && k < K) __builtin_nontemporal_store(o, reinterpret_cast<ovec*>(dst + (int64_t)L * k));
+        ovec* z = reinterpret_cast<ovec*>(dst + (int64_t)L * k);
+        if (cok && k < K) {
+          if constexpr (NT) __builtin_nontemporal_store(o, z);
+          else *z = o;
+        }
       }
     }
   };
@@ -684,13 +693,16 @@ void launch_ttm_slab(const TI* Y, int J, uint64_t L, uint64_t cols, const double
   const int64_t nct = ceil_div((int64_t)cols, 32);
   const int64_t grid = std::min<int64_t>(ceil_div(nct, 4), 256 * 4);
   const int rb = (int)ceil_div(K, 16);
-#define TS_LAUNCH(RBV, NJV)                                                                                    \
-  hipLaunchKernelGGL((ttm_slab_kernel<TI, TO, CT, RBV, NJV>), dim3(grid), dim3(256), 0, stream, Y, J,       \
+  const bool nt = L * sizeof(TO) % 64 == 0 && reinterpret_cast<uintptr_t>(Z) % 64 == 0;
+#define TS_LAUNCH(RBV, NJV, NTV)                                                                                \
+  hipLaunchKernelGGL((ttm_slab_kernel<TI, TO, CT, RBV, NJV, NTV>), dim3(grid), dim3(256), 0, stream, Y, J,      \
                      (uint32_t)L, (uint32_t)cols, M, msk, msj, K, Z, nct)
-#define TS_NJ(RBV)                       \
-  do {                                   \
-    if (J <= 16) TS_LAUNCH(RBV, 1);      \
-    else TS_LAUNCH(RBV, 2);              \
+#define TS_NJ(RBV)                                  \
+  do {                                              \
+    if (J <= 16 && nt) TS_LAUNCH(RBV, 1, true);     \
+    else if (J <= 16) TS_LAUNCH(RBV, 1, false);     \
+    else if (nt) TS_LAUNCH(RBV, 2, true);           \
+    else TS_LAUNCH(RBV, 2, false);                  \
   } while (0)
   if (rb == 1) TS_NJ(1);
   else if (rb == 2) TS_NJ(2);
@@ -703,15 +715,29 @@ void launch_ttm_slab(const TI* Y, int J, uint64_t L, uint64_t cols, const double
 template <typename TI, typename TO, typename CT>
 hipError_t launch_ttm_ct(const TI* Y, int J, uint64_t L, uint64_t cols, const double* M, int64_t msk, int64_t msj,
                          int K, TO* Z, hipStream_t stream) {
-  // pairs of columns on both sides; past 32 rows the resident kernel's loads
-  // of several blocks are in flight anyway (33 -> 33 rows: 5.1 TB/s).  Shorter
-  // slabs leave partial lines to write (L = 2, 4 -> 27 rows: 0.12 ms for 2
-  // million columns in the resident kernel, 0.31 ms here; L = 64: 0.24 and
-  // 0.11 ms); with slabs that hold whole tiles of the resident kernel, many sums
-  // per lane cost more than its passes (L = 5000: 32 -> 50 rows 0.24 and 0.30 ms,
-  // 11 -> 50 the same, 11 -> 12 0.08 and 0.06 ms), as do many rows for few sums
-  // (32 -> 3 rows: 0.104 and 0.112 ms).
-  if (L >= 64 && L % 2 == 0 && J <= 32 && K <= 64 && J <= 8 * K && (L <= 96 || (K <= 50 && J * K <= 900)) &&
+  // Pairs of columns on both sides, up to two reduction blocks (past 32 rows the
+  // resident kernel's loads of several blocks are in flight anyway: 33 -> 33
+  // rows 5.1 TB/s) and four row blocks.  Resident against slab kernel, us, for 2
+  // million columns of doubles to floats, in slabs of L = 256 (whole 64-byte
+  // pieces) and 1000 (not):
+  //   4 -> 27   97 / 48, 109 / 85    12 -> 50 203 / 95, 206 / 168   12 -> 52 206 / 96, 209 / 172
+  //   32 -> 16 138 / 123, 161 / 143  32 -> 50 229 / 181, 240 / 232  32 -> 64 247 / 193, 282 / 274
+  // so the output's rows set no line: K of 3 to 64 and J of 1 to 32 on 17 lengths
+  // of slab, in four type combinations, measured 0.96 to 2.9 times as fast, but for
+  //  * many rows for few sums: 32 -> 3 rows 105 and 111;
+  //  * the most sums from doubles to doubles: 32 -> 64 rows 287 and 301;
+  //  * small products, where a wave has a tile or two and no next one to load
+  //    ahead.  5387 shapes put the line at a number of words read and written that
+  //    grows with the square of J, and doubles for float output and for FP32
+  //    products (on this side of it nine shapes at 0.89 to 0.94, the others above).
+  //    Doubles to floats, L = 1000: 8 -> 16 rows of 2^16 columns 6.2 / 6.5, of 2^17
+  //    7.3 / 6.4; 32 -> 27 of 2^18 20.9 / 24.6, of 2^19 38.1 / 38.4; FP32, 32 -> 64
+  //    of 2^18 25.3 / 28.7, of 2^19 49.0 / 42.7.
+  // Slabs of L < 64 (0.74 to 2.4 times) stay where they were.
+  const uint64_t words = cols * (uint64_t)(J + K);
+  const uint64_t few = ((uint64_t)J * (uint64_t)J) << (13 + (sizeof(TO) == 4) + (sizeof(CT) == 4));
+  if (L >= 64 && L % 2 == 0 && J <= 32 && K <= 64 && J <= 8 * K && words >= std::max<uint64_t>(few, 5 << 19) &&
+      (sizeof(TI) == 4 || sizeof(TO) == 4 || J * K < 32 * 64) &&
       reinterpret_cast<uintptr_t>(Y) % (2 * sizeof(TI)) == 0 &&
       reinterpret_cast<uintptr_t>(Z) % (2 * sizeof(TO)) == 0) {
     launch_ttm_slab<TI, TO, CT>(Y, J, L, cols, M, msk, msj, K, Z, stream);

@@ -238,3 +238,73 @@ def test_ttm_on_a_full_device_waits_for_nothing(tk):
         torch.cuda.synchronize()
         del filler
         torch.cuda.empty_cache()
+
+
+# what ttm_slab_kernel takes: an even slab of at least 64 columns, enough words
+# read and written (slab_words); one and two reduction blocks, whole, ragged and
+# of one row; one to four row blocks, whole and ragged; rows of Z in whole
+# 64-byte pieces and not; tiles that straddle slabs and a last one that the
+# columns do not fill
+SLABS = [
+    (64, 20500, 1, 1), (64, 4097, 16, 16), (66, 3973, 5, 17), (96, 2731, 12, 50), (98, 2675, 16, 33),
+    (1024, 257, 4, 64), (100, 3000, 7, 2), (202, 1299, 12, 51),
+    (64, 8193, 17, 16), (66, 7945, 31, 32), (96, 5462, 32, 33), (1000, 525, 20, 50), (200, 2622, 32, 63),
+    (66, 7945, 17, 64), (80, 8300, 24, 5), (64, 8193, 32, 64),
+]
+
+
+def slab_words(J):
+    return max(5 << 19, J * J << 15)  # for FP32 products to floats, the most of all
+
+
+def slab_check(tk, L, R, J, K, ydt, zdt, fp32, layout, zoff=0):
+    g = torch.Generator(device="cuda").manual_seed(L + J + K)
+    y = torch.randn(R, J, L, dtype=torch.float64, device="cuda", generator=g).to(ydt)
+    M = torch.randn(K, J, dtype=torch.float64, device="cuda", generator=g)
+    m = M if layout == "rows" else M.t().contiguous().t()
+    buf = torch.full((R * K * L + 2 * zoff,), 7.0, dtype=zdt, device="cuda")
+    z = buf[zoff:zoff + R * K * L].view(R, K, L)
+    code = {torch.float32: tk.F32, torch.float64: tk.F64}
+    st = tk.lib().tucker_ttm(y.data_ptr(), code[ydt], tk._i64([L, J, R]), 3, 1, m.data_ptr(), K, m.stride(0),
+                             m.stride(1), z.data_ptr(), code[zdt], int(fp32), tk._stream())
+    assert st == 0
+    cols = y.double().permute(1, 0, 2).reshape(J, R * L).contiguous()
+    ref, mag = M @ cols, M.abs() @ cols.abs()
+    tol = 1e-12 * mag
+    if zdt == torch.float32:
+        tol = tol + 2.0 ** -23 * ref.abs()
+    if fp32:
+        tol = tol + (J + 2) * 2.0 ** -23 * mag
+    d = (z.double().permute(1, 0, 2).reshape(K, R * L) - ref).abs()
+    assert bool((d <= tol).all()), (L, R, J, K, ydt, zdt, fp32, layout)
+    assert bool((buf[:zoff] == 7.0).all()) and bool((buf[zoff + R * K * L:] == 7.0).all())
+
+
+@pytest.mark.parametrize("L,R,J,K", SLABS)
+def test_ttm_slab_kernel(tk, L, R, J, K):
+    assert L * R * (J + K) >= slab_words(J) and J <= 8 * K
+    f32, f64 = torch.float32, torch.float64
+    for ydt, zdt, fp32 in ((f64, f64, False), (f64, f32, False), (f32, f64, False), (f32, f32, False),
+                           (f32, f32, True), (f64, f64, True)):
+        slab_check(tk, L, R, J, K, ydt, zdt, fp32, "columns")
+    slab_check(tk, L, R, J, K, f32, f64, False, "rows")
+    # Z past a 64-byte boundary
+    slab_check(tk, L, R, J, K, f64, f64, False, "columns", zoff=2)
+    slab_check(tk, L, R, J, K, f32, f32, True, "columns", zoff=2)
+
+
+@pytest.mark.parametrize("L,R,J", [(64, 4097, 5), (66, 4500, 13), (96, 5462, 21), (66, 12200, 30)])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_ttm_slab_infinity(tk, L, R, J, fp32):
+    """Rows past J, which hold a repeated row, are not multiplied in: an
+    infinity in the last row stays in its own column."""
+    assert L * R * (J + 7) >= slab_words(J)
+    dt = torch.float32 if fp32 else torch.float64
+    y = torch.zeros((R, J, L), dtype=dt, device="cuda")
+    y[1, J - 1, 3] = float("inf")
+    y[R - 1, J - 1, L - 1] = float("-inf")
+    z = tk.ttm(y, 1, torch.ones((7, J), dtype=torch.float64, device="cuda"), fp32_products=fp32)
+    want = torch.zeros((R, 7, L), dtype=dt, device="cuda")
+    want[1, :, 3] = float("inf")
+    want[R - 1, :, L - 1] = float("-inf")
+    assert torch.equal(z, want)
