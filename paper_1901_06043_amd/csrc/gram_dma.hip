@@ -528,11 +528,19 @@ static bool gram_dma_w16(int J, uint64_t L, int elem_size, const void* Y) {
 // which the register-staged tile pairs multiply, but takes its chunks slab by
 // slab, so a last chunk that a short slab does not fill is work as well.
 // `gain` is the block products of the one over those of the other.  With
-// 16-byte loads FP64 and, on filled chunks, FP32 are the faster here whatever
-// the gain (FP32, 256 rows: 3.2 against 3.9 ms); with 4-byte loads, whose
-// issue the products no longer cover, and for BF16X6, whose pieces are made
-// again by every wave, the lines lie where the two measured the same.  Register-
-// staged against here, in ms, 400000 columns in slabs of L, J at gain:
+// 16-byte loads FP64 and, on filled chunks, FP32 are taken here whatever the
+// gain (FP32, 256 rows: 3.2 against 3.9 ms; FP64 of doubles at least 1.04 times as
+// fast, of floats in slabs that fill three quarters of their chunks, at a gain
+// of 0.83 to 0.91, 0.93 to 0.97); with 4-byte loads, whose issue the products no
+// longer cover, and for BF16X6, whose pieces are made again by every wave, the
+// lines lie where the two measured the same.  Doubles (chunks of 16 columns, two
+// 4-byte loads a value) cross at the same gains as floats but for three tiles.
+// Register-staged against here, in ms, columns in slabs of L, J at gain:
+//   FP64 of doubles, 300000 columns:
+//          L =  65: 250 at 1.15 0.65 / 0.70, 384 at 1.04 1.29 / 1.41, 512 at 0.98 2.16 / 2.11
+//          L =  67: 256 at 1.18 0.66 / 0.66, 384 at 1.07 1.30 / 1.37, 626 at 0.98 3.19 / 3.10
+//          L = 129: 256 at 1.26 0.65 / 0.61, 384 at 1.15 1.28 / 1.26, 672 at 1.33 4.38 / 3.41
+//   400000 columns of floats:
 //   FP64   L =  67: 250 at 0.99 0.83 / 0.87, 336 at 1.16 1.62 / 1.48, 626 at 0.82 4.03 / 4.40
 //   FP32   L = 447: 200 at 2.11 0.45 / 0.35, 336 at 1.66 0.87 / 0.86, 626 at 1.17 2.13 / 2.83
 //          L = 161: 161 at 2.44 0.45 / 0.35, 200 at 1.77 0.45 / 0.41, 336 at 1.39 0.88 / 1.01
@@ -542,7 +550,7 @@ static bool rows_pay(int J, uint64_t L, int elem_size, bool w16, int prec) {
   const int64_t KC = 128 / elem_size, nt = ceil_div(J, 128), nb = ceil_div(J, 16);
   const double fill = (double)L / (double)(ceil_div((int64_t)L, KC) * KC);
   const double gain = 64.0 * (double)(nt * (nt + 1)) / (double)(nb * (nb + 1)) * fill;
-  if (prec == 0) return w16 || gain >= (nt == 2 ? 1.2 : 1.0);
+  if (prec == 0) return w16 || gain >= (nt == 2 ? 1.2 : nt == 3 && elem_size == 8 ? 1.1 : 1.0);
   if (prec == 1) return gain >= 1.72 || (w16 && fill >= 0.95);
   return gain >= 2.05;
 }

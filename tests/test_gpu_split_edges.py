@@ -174,3 +174,16 @@ def test_tridiagonalisation_phase_edges(tk, J):
     assert R == (J if J <= 31 else J - 17)
     assert np.abs(U.T @ U - np.eye(R)).max() <= 1e-11
     assert np.linalg.norm(S @ U - U * lam[:R], 2) <= 1e-11 * ref[0]
+
+
+# double rows that are not 16-byte aligned, on both sides of the lines between
+# the tile-pair kernels (two, three and four tiles)
+@pytest.mark.parametrize("L,J", [(67, 250), (129, 250), (65, 384), (67, 384), (129, 384), (65, 300), (65, 512)])
+def test_double_row_segments(tk, orc, L, J):
+    dims = [L, J, 9]
+    X = np.random.default_rng(L + J).standard_normal(int(np.prod(dims)))
+    S, nrm = tk.gram(to_dev(X, dims, torch.float64), 1, dims=dims, with_norm=True)
+    ref = orc.gram(X, dims, 1)
+    d = np.sqrt(np.outer(np.diag(ref), np.diag(ref)))
+    assert np.all(np.abs(S.cpu().numpy() - ref) <= 1e-11 * d)
+    assert abs(float(nrm[0]) - np.dot(X, X)) <= 1e-12 * np.dot(X, X)
