@@ -114,33 +114,58 @@ __device__ __forceinline__ Mom mom_load(const double* p) {
 }
 
 // Tree merge of one Mom per thread over NT threads (fixed order); the result
-// is valid in thread 0.
+// is valid in thread 0.  `active` (uniform): threads from it on hold an empty
+// Mom, and the tree's levels above it are left out.  One row of LDS per
+// member: with a Mom's members side by side the lanes of a wave met in four
+// banks.
 template <int NT>
-__device__ __forceinline__ Mom block_merge(Mom s, double (*sh)[kMW]) {
+__device__ __forceinline__ Mom block_merge(Mom s, double (*sh)[NT], uint64_t active) {
   const int tid = threadIdx.x;
-  mom_store(sh[tid], s);
+  auto put = [&](const Mom& m) __attribute__((always_inline)) {
+    const double v[kMW] = {m.cnt, m.mean, m.m2, m.sum, m.mn, m.mx, m.n1, m.n2};
+#pragma unroll
+    for (int k = 0; k < kMW; ++k) sh[k][tid] = v[k];
+  };
+  put(s);
   __syncthreads();
   for (int w = NT / 2; w > 0; w >>= 1) {
+    if ((uint64_t)w >= active) continue;
     if (tid < w) {
-      mom_merge(s, mom_load(sh[tid + w]));
-      mom_store(sh[tid], s);
+      const int o = tid + w;
+      mom_merge(s, Mom{sh[0][o], sh[1][o], sh[2][o], sh[3][o], sh[4][o], sh[5][o], sh[6][o], sh[7][o]});
+      put(s);
     }
     __syncthreads();
   }
   return s;
 }
 
+// The statistics of slice a: stats[s*J + a] for mean, standard deviation, min,
+// max, 1-norm, 2-norm.
+__device__ __forceinline__ void mom_stats(const Mom& t, uint64_t a, uint64_t J, double* __restrict__ stats) {
+  stats[0 * J + a] = t.sum / t.cnt;
+  stats[1 * J + a] = sqrt(t.m2 / t.cnt);
+  stats[2 * J + a] = t.mn;
+  stats[3 * J + a] = t.mx;
+  stats[4 * J + a] = t.n1;
+  stats[5 * J + a] = sqrt(t.n2);
+}
+
 // Row mapping: workgroup (a, s) reduces columns [s*cper, (s+1)*cper) of
 // slice a.  Column c of the unfolding is (r, l) = divmod(c, L).  V values per
 // load (V > 1: L and cper multiples of V, Y aligned to V values), 16 values
-// per thread in flight.
-template <typename T, int V>
-__global__ __launch_bounds__(kST) void slice_rows_kernel(const T* __restrict__ Y, uint64_t L, uint64_t J,
+// per thread in flight.  Slices in one piece (nsplit = 1: many, or short ones)
+// get their statistics here, without a second launch (10 us for 5000 slices).
+// NT threads: one wave where that holds a split's values, so that a CU reduces
+// four times as many of them at once (5000 slices of 198 floats: 37 us with four
+// waves, 14 us with one).
+template <typename T, int V, int NT>
+__global__ __launch_bounds__(NT) void slice_rows_kernel(const T* __restrict__ Y, uint64_t L, uint64_t J,
                                                          uint64_t Rt, int64_t nsplit, uint64_t cper,
-                                                         double* __restrict__ part) {
+                                                         double* __restrict__ part, double* __restrict__ stats) {
   constexpr int B = 16, NL = B / V;
   typedef T vec __attribute__((ext_vector_type(V)));
-  __shared__ double sh[kST][kMW];
+  __shared__ double sh[kMW][NT];
   const uint64_t a = blockIdx.x / nsplit;
   const uint64_t s = blockIdx.x - a * nsplit;
   const uint64_t K = L * Rt;
@@ -148,7 +173,7 @@ __global__ __launch_bounds__(kST) void slice_rows_kernel(const T* __restrict__ Y
   const uint64_t c1 = (c0 + cper < K) ? c0 + cper : K;
   Mom acc;
   mom_init(acc);
-  constexpr uint64_t kStep = (uint64_t)kST * V;
+  constexpr uint64_t kStep = (uint64_t)NT * V;
   uint64_t c = c0 + (uint64_t)threadIdx.x * V;
   uint64_t r = c / L, l = c - r * L;
   const uint64_t dr = kStep / L;
@@ -184,8 +209,10 @@ __global__ __launch_bounds__(kST) void slice_rows_kernel(const T* __restrict__ Y
     }
     mom_batch<B>(acc, x, nb);
   }
-  acc = block_merge<kST>(acc, sh);
-  if (threadIdx.x == 0) mom_store(part + (a * nsplit + s) * kMW, acc);
+  acc = block_merge<NT>(acc, sh, (c1 - c0 + V - 1) / V);
+  if (threadIdx.x != 0) return;
+  if (nsplit == 1) mom_stats(acc, a, J, stats);
+  else mom_store(part + (a * nsplit + s) * kMW, acc);
 }
 
 // Period mapping: workgroup w reduces the groups of G periods [w*gper,
@@ -237,32 +264,44 @@ __global__ __launch_bounds__(kST) void slice_period_kernel(const T* __restrict__
     }
     __syncthreads();
   }
-  for (uint32_t a = tid; a < J; a += kST) {
-    Mom t = mom_load(sp[a * L]);
-    for (uint32_t l = 1; l < L; ++l) mom_merge(t, mom_load(sp[a * L + l]));
-    mom_store(part + ((uint64_t)blockIdx.x * J + a) * kMW, t);
+  // (short ones one after the other, on up to 256 slices at once; 63 merges of one
+  // slice took 5 us that way)
+  if (L < 8) {
+    for (uint32_t a = tid; a < J; a += kST) {
+      Mom t = mom_load(sp[a * L]);
+      for (uint32_t l = 1; l < L; ++l) mom_merge(t, mom_load(sp[a * L + l]));
+      mom_store(part + ((uint64_t)blockIdx.x * J + a) * kMW, t);
+    }
+    return;
   }
+  for (uint32_t n = L; n > 1; n = (n + 1) / 2) {
+    const uint32_t h = (n + 1) / 2;
+    for (uint32_t i = tid; i < J * h; i += kST) {
+      const uint32_t a = i / h, l = i - a * h;
+      if (l + h < n) {
+        Mom t = mom_load(sp[a * L + l]);
+        mom_merge(t, mom_load(sp[a * L + l + h]));
+        mom_store(sp[a * L + l], t);
+      }
+    }
+    __syncthreads();
+  }
+  for (uint32_t a = tid; a < J; a += kST)
+    mom_store(part + ((uint64_t)blockIdx.x * J + a) * kMW, mom_load(sp[a * L]));
 }
 
 // One wave per slice: the partials (stride sa between slices, ss between
-// splits) in a fixed order.  stats[s*J + a]: mean, standard deviation, min,
-// max, 1-norm, 2-norm.
+// splits) in a fixed order.
 __global__ __launch_bounds__(64) void slice_finalize_kernel(const double* __restrict__ part, uint64_t J,
                                                             int64_t nsplit, uint64_t sa, uint64_t ss,
                                                             double* __restrict__ stats) {
-  __shared__ double sh[64][kMW];
+  __shared__ double sh[kMW][64];
   const uint64_t a = blockIdx.x;
   Mom t;
   mom_init(t);
   for (int64_t s = threadIdx.x; s < nsplit; s += 64) mom_merge(t, mom_load(part + a * sa + s * ss));
-  t = block_merge<64>(t, sh);
-  if (threadIdx.x != 0) return;
-  stats[0 * J + a] = t.sum / t.cnt;
-  stats[1 * J + a] = sqrt(t.m2 / t.cnt);
-  stats[2 * J + a] = t.mn;
-  stats[3 * J + a] = t.mx;
-  stats[4 * J + a] = t.n1;
-  stats[5 * J + a] = sqrt(t.n2);
+  t = block_merge<64>(t, sh, (uint64_t)nsplit);
+  if (threadIdx.x == 0) mom_stats(t, a, J, stats);
 }
 
 __global__ __launch_bounds__(kST) void scaling_vectors_kernel(const double* __restrict__ stats, uint64_t J,
@@ -528,10 +567,19 @@ hipError_t launch_slice_stats(const T* Y, uint64_t L, uint64_t J, uint64_t Rt, d
   } else {
     constexpr int V = 16 / sizeof(T);
     const dim3 grid(J * p.nsplit);
-    if (L % V == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0)
-      hipLaunchKernelGGL((slice_rows_kernel<T, V>), grid, dim3(kST), 0, s, Y, L, J, Rt, p.nsplit, p.per, work);
-    else
-      hipLaunchKernelGGL((slice_rows_kernel<T, 1>), grid, dim3(kST), 0, s, Y, L, J, Rt, p.nsplit, p.per, work);
+    const bool vec = L % V == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
+#define SR_LAUNCH(VV, NTV)                                                                                       \
+  hipLaunchKernelGGL((slice_rows_kernel<T, VV, NTV>), grid, dim3(NTV), 0, s, Y, L, J, Rt, p.nsplit, p.per, work, \
+                     stats)
+    if (p.per <= 16 * 64) {
+      if (vec) SR_LAUNCH(V, 64);
+      else SR_LAUNCH(1, 64);
+    } else {
+      if (vec) SR_LAUNCH(V, kST);
+      else SR_LAUNCH(1, kST);
+    }
+#undef SR_LAUNCH
+    if (p.nsplit == 1) return hipGetLastError();
   }
   const uint64_t sa = p.period ? kMW : (uint64_t)p.nsplit * kMW, ss = p.period ? J * kMW : kMW;
   hipLaunchKernelGGL(slice_finalize_kernel, dim3(J), dim3(64), 0, s, work, J, p.nsplit, sa, ss, stats);

@@ -187,3 +187,21 @@ def test_double_row_segments(tk, orc, L, J):
     d = np.sqrt(np.outer(np.diag(ref), np.diag(ref)))
     assert np.all(np.abs(S.cpu().numpy() - ref) <= 1e-11 * d)
     assert abs(float(nrm[0]) - np.dot(X, X)) <= 1e-12 * np.dot(X, X)
+
+
+# slices in one piece, whose statistics the first kernel writes: many, and short
+# ones; one wave and four per slice; both orders of merging a period's values
+@pytest.mark.parametrize("dims,n", [
+    ([66, 2500, 3], 1), ([5, 3000, 1], 1), ([1, 4100, 2], 1), ([64, 2048, 17], 1), ([65, 33, 15], 1), ([1025, 3], 1),
+    ([7, 140, 3], 1), ([8, 128, 3], 1), ([63, 3, 3], 1), ([1, 1024, 2], 1),
+])
+def test_slice_stats_whole_slices(tk, orc, dims, n):
+    rng = np.random.default_rng(sum(dims))
+    X = rng.standard_normal(int(np.prod(dims))) * 2.0 + 1.0e3
+    st = tk.slice_stats(to_dev(X, dims, torch.float64), n, dims=dims).cpu().numpy()
+    ref = orc.slice_stats(X, dims, n)
+    cnt = X.size // dims[n]
+    np.testing.assert_array_equal(st[2:4], ref[2:4])
+    assert np.all(np.abs(st[0] - ref[0]) <= 1e-12 * ref[4] / cnt)
+    assert np.all(np.abs(st[1] - ref[1]) <= 1e-12 * ref[5] / np.sqrt(cnt))
+    np.testing.assert_allclose(st[4:], ref[4:], rtol=1e-12)
