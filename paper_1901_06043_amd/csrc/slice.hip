@@ -351,19 +351,21 @@ __device__ __forceinline__ TO affine(TI x, double sh, double sc) {
 }
 
 // Y = (X - shift_a) / scale_a (or the inverse fma(X, scale_a, shift_a)) with
-// a the slice of each element.  A thread takes 4 groups of 4 consecutive
+// a the slice of each element.  A thread takes U groups of 4 consecutive
 // elements per iteration, all loaded before the first is used, and carries
-// (l, a) of each group's first element incrementally.  With one group per
-// iteration the map took 2.02 ms on the 672x672x33x64 float32 tensor (3.8 TB/s
-// read and written), now 1.57 ms (4.9 TB/s).
+// (l, a) of each group's first element incrementally.  One group per iteration
+// takes 2.02 ms on the 672x672x33x64 float32 tensor (3.8 TB/s read and written),
+// four 1.57 ms (4.9 TB/s), where the scaling is looked up again only where the
+// slice changes.  That branch is taken in most groups of short odd slices: there,
+// and for few groups per thread, one group, each element looking up its own
+// (5x200x30000 floats: 44 us, with four groups 59 us).
 // X and Y may be the same buffer (in place; each thread reads its elements
 // before writing them).
-template <typename TI, typename TO, bool INV>
+template <typename TI, typename TO, bool INV, int U>
 __global__ __launch_bounds__(kST) void slice_transform_kernel(const TI* X, TO* Y,
                                                               uint64_t total, uint64_t L, uint64_t J,
                                                               const double* __restrict__ shift,
                                                               const double* __restrict__ scale) {
-  constexpr int U = 4;
   const uint64_t nvec = total / 4;
   const uint64_t stride = (uint64_t)gridDim.x * kST;
   uint64_t v = (uint64_t)blockIdx.x * kST + threadIdx.x;
@@ -372,50 +374,74 @@ __global__ __launch_bounds__(kST) void slice_transform_kernel(const TI* X, TO* Y
   uint64_t a = q % J;
   const uint64_t S = 4 * stride;
   const uint64_t dq = S / L, dl = S - dq * L, da = dq % J;
-  while (v < nvec) {
-    TI x[U][4];
-    uint64_t lv[U], av[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      lv[u] = l;
-      av[u] = a;
-      const uint64_t at = v + u * stride;
-      if (at < nvec) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[u][j] = X[4 * at + j];
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[u][j] = (TI)0;
-      }
-      l += dl;
-      a += da;
-      if (l >= L) {
-        l -= L;
-        ++a;
-      }
-      while (a >= J) a -= J;
+  auto step = [&]() __attribute__((always_inline)) {
+    l += dl;
+    a += da;
+    if (l >= L) {
+      l -= L;
+      ++a;
     }
+    while (a >= J) a -= J;
+  };
+  if constexpr (U == 1) {
+    for (; v < nvec; v += stride) {
+      TI x[4];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint64_t at = v + u * stride;
-      if (at >= nvec) break;
-      uint64_t lc = lv[u], ac = av[u];
+      for (int j = 0; j < 4; ++j) x[j] = X[4 * v + j];
+      uint64_t lc = l, ac = a;
       TO y[4];
-      double sh = shift[ac], sc = scale[ac];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        y[j] = affine<TI, TO, INV>(x[u][j], sh, sc);
-        if (++lc == L && j < 3) {
+        y[j] = affine<TI, TO, INV>(x[j], shift[ac], scale[ac]);
+        if (++lc == L) {
           lc = 0;
           ac = (ac + 1 == J) ? 0 : ac + 1;
-          sh = shift[ac];
-          sc = scale[ac];
         }
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) Y[4 * at + j] = y[j];
+      for (int j = 0; j < 4; ++j) Y[4 * v + j] = y[j];
+      step();
     }
-    v += U * stride;
+  } else {
+    while (v < nvec) {
+      TI x[U][4];
+      uint64_t lv[U], av[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        lv[u] = l;
+        av[u] = a;
+        const uint64_t at = v + u * stride;
+        if (at < nvec) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[u][j] = X[4 * at + j];
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[u][j] = (TI)0;
+        }
+        step();
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint64_t at = v + u * stride;
+        if (at >= nvec) break;
+        uint64_t lc = lv[u], ac = av[u];
+        TO y[4];
+        double sh = shift[ac], sc = scale[ac];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          y[j] = affine<TI, TO, INV>(x[u][j], sh, sc);
+          if (++lc == L && j < 3) {
+            lc = 0;
+            ac = (ac + 1 == J) ? 0 : ac + 1;
+            sh = shift[ac];
+            sc = scale[ac];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) Y[4 * at + j] = y[j];
+      }
+      v += U * stride;
+    }
   }
   // the last total % 4 elements
   if (blockIdx.x == 0 && threadIdx.x < total - 4 * nvec) {
@@ -608,12 +634,19 @@ hipError_t launch_slice_transform(const TI* X, TO* Y, uint64_t total, uint64_t L
                                   const double* scale, bool inverse, hipStream_t s) {
   const uint64_t nvec = total / 4;
   const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div((int64_t)nvec, kST), 8192));
-  if (inverse)
-    hipLaunchKernelGGL((slice_transform_kernel<TI, TO, true>), dim3(grid), dim3(kST), 0, s, X, Y, total, L, J, shift,
-                       scale);
-  else
-    hipLaunchKernelGGL((slice_transform_kernel<TI, TO, false>), dim3(grid), dim3(kST), 0, s, X, Y, total, L, J, shift,
-                       scale);
+  // the time of one group at a time over that of four, 33 slices of floats: 4.0e8
+  // elements, L = 64 (whole groups) 1.32, 255 1.17, 129 0.98, 65 0.86; L = 64, 2.4e7
+  // elements (3 groups a thread) 0.88, 3.4e7 (4) 1.01, 5.0e7 1.27; of doubles (or to
+  // them) 1.2e7 (1.5) 0.98, 2.4e7 1.09
+  const bool four = (L % 4 == 0 || L >= 192) && 2 * nvec >= (uint64_t)((sizeof(TI) + sizeof(TO) > 8 ? 5 : 8) * grid * kST);
+#define ST_LAUNCH(INV, U)                                                                                        \
+  hipLaunchKernelGGL((slice_transform_kernel<TI, TO, INV, U>), dim3(grid), dim3(kST), 0, s, X, Y, total, L, J, shift, \
+                     scale)
+  if (inverse && four) ST_LAUNCH(true, 4);
+  else if (inverse) ST_LAUNCH(true, 1);
+  else if (four) ST_LAUNCH(false, 4);
+  else ST_LAUNCH(false, 1);
+#undef ST_LAUNCH
   return hipGetLastError();
 }
 

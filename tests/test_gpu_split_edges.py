@@ -205,3 +205,20 @@ def test_slice_stats_whole_slices(tk, orc, dims, n):
     assert np.all(np.abs(st[0] - ref[0]) <= 1e-12 * ref[4] / cnt)
     assert np.all(np.abs(st[1] - ref[1]) <= 1e-12 * ref[5] / np.sqrt(cnt))
     np.testing.assert_allclose(st[4:], ref[4:], rtol=1e-12)
+
+
+# enough elements for four groups per thread and iteration: whole groups, groups
+# that straddle slices, a last iteration and a last group that are not full
+@pytest.mark.parametrize("dims", [[64, 33, 15903], [193, 33, 5311], [201, 7, 23999]])
+@pytest.mark.parametrize("dt", [torch.float32, torch.float64])
+def test_slice_transform_large(tk, dims, dt):
+    L, J, R = dims
+    g = torch.Generator(device="cuda").manual_seed(L)
+    x = torch.randn(R, J, L, device="cuda", dtype=dt, generator=g)
+    sh = torch.randn(J, device="cuda", dtype=torch.float64, generator=g)
+    sc = torch.rand(J, device="cuda", dtype=torch.float64, generator=g) + 0.5
+    y = tk.slice_transform(x, 1, sh, sc, dims=dims)
+    want = ((x.double() - sh[:, None]) / sc[:, None]).to(dt)
+    assert torch.equal(y, want)
+    back = tk.slice_transform(y, 1, sh, sc, dims=dims, inverse=True)
+    assert bool(((back - x).abs() <= (2.0 ** -21 if dt == torch.float32 else 1e-14) * (x.abs() + 4.0)).all())
