@@ -433,7 +433,7 @@ tucker_status run_gram(const void* Y, tucker_dtype dt, const int64_t* dims, int 
   }
   const int es = (dt == TUCKER_F64) ? 8 : 4;
   const int dprec = dma_gram_prec(prec);
-  if (dprec >= 0 && tk::gram_dma_eligible((int)J, (uint64_t)L, es, Y, dprec)) {
+  if (dprec >= 0 && tk::gram_dma_eligible((int)J, (uint64_t)L, (uint64_t)K, es, Y, dprec)) {
     // larger modes, every form but BF16X3: tile pairs staged by direct
     // global-to-LDS loads
     tk::GramPlan p = tk::plan_gram_dma((int)J, (uint64_t)L, (uint64_t)K, es, dprec);
@@ -667,7 +667,7 @@ int64_t gram_scratch_doubles(const int64_t* dims, int N, int n, tucker_gram_prec
     // reduced forms: float input)
     for (int es : {4, 8}) {
       if (dprec >= 1 && es == 8) continue;
-      if (tk::gram_dma_eligible((int)J, (uint64_t)L, es, nullptr, dprec)) {
+      if (tk::gram_dma_eligible((int)J, (uint64_t)L, (uint64_t)K, es, nullptr, dprec)) {
         const tk::GramPlan d = tk::plan_gram_dma((int)J, (uint64_t)L, (uint64_t)K, es, dprec);
         need = std::max(need, d.part_elems + d.sq_elems);
       }

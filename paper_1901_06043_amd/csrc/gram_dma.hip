@@ -524,56 +524,81 @@ static bool gram_dma_w16(int J, uint64_t L, int elem_size, const void* Y) {
   return ((L == 1 ? (uint64_t)J : L) * (uint64_t)elem_size) % 16 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
 }
 
-// Row segments: this kernel leaves out the blocks past J of a ragged last tile,
-// which the register-staged tile pairs multiply, but takes its chunks slab by
-// slab, so a last chunk that a short slab does not fill is work as well.
-// `gain` is the block products of the one over those of the other.  With
-// 16-byte loads FP64 and, on filled chunks, FP32 are taken here whatever the
-// gain (FP32, 256 rows: 3.2 against 3.9 ms; FP64 of doubles at least 1.04 times as
-// fast, of floats in slabs that fill three quarters of their chunks, at a gain
-// of 0.83 to 0.91, 0.93 to 0.97); with 4-byte loads, whose issue the products no
-// longer cover, and for BF16X6, whose pieces are made again by every wave, the
-// lines lie where the two measured the same.  Doubles (chunks of 16 columns, two
-// 4-byte loads a value) cross at the same gains as floats but for three tiles.
-// Register-staged against here, in ms, columns in slabs of L, J at gain:
-//   FP64 of doubles, 300000 columns:
-//          L =  65: 250 at 1.15 0.65 / 0.70, 384 at 1.04 1.29 / 1.41, 512 at 0.98 2.16 / 2.11
-//          L =  67: 256 at 1.18 0.66 / 0.66, 384 at 1.07 1.30 / 1.37, 626 at 0.98 3.19 / 3.10
-//          L = 129: 256 at 1.26 0.65 / 0.61, 384 at 1.15 1.28 / 1.26, 672 at 1.33 4.38 / 3.41
-//   400000 columns of floats:
-//   FP64   L =  67: 250 at 0.99 0.83 / 0.87, 336 at 1.16 1.62 / 1.48, 626 at 0.82 4.03 / 4.40
-//   FP32   L = 447: 200 at 2.11 0.45 / 0.35, 336 at 1.66 0.87 / 0.86, 626 at 1.17 2.13 / 2.83
-//          L = 161: 161 at 2.44 0.45 / 0.35, 200 at 1.77 0.45 / 0.41, 336 at 1.39 0.88 / 1.01
-//   BF16X6 L = 447: 161 at 2.91 0.40 / 0.33, 200 at 2.11 0.42 / 0.38, 336 at 1.66 0.85 / 0.96
-//          L =  67: 161 at 2.03 0.40 / 0.46; 16-byte loads, 512 at 1.21 4.24 / 4.60
-static bool rows_pay(int J, uint64_t L, int elem_size, bool w16, int prec) {
-  const int64_t KC = 128 / elem_size, nt = ceil_div(J, 128), nb = ceil_div(J, 16);
-  const double fill = (double)L / (double)(ceil_div((int64_t)L, KC) * KC);
-  const double gain = 64.0 * (double)(nt * (nt + 1)) / (double)(nb * (nb + 1)) * fill;
-  if (prec == 0) return w16 || gain >= (nt == 2 ? 1.2 : nt == 3 && elem_size == 8 ? 1.1 : 1.0);
-  if (prec == 1) return gain >= 1.72 || (w16 && fill >= 0.95);
-  return gain >= 2.05;
+// Work items: tile pairs by splits of at least 16 chunks, up to about 8192.
+static int64_t gram_dma_chunks(uint64_t L, uint64_t K, int elem_size) {
+  const int64_t KC = (L == 1 && elem_size == 8) ? Img<8, 0>::KC : 128 / elem_size;
+  return (L == 1) ? ceil_div((int64_t)K, KC) : (int64_t)(K / L) * ceil_div((int64_t)L, KC);
+}
+static int64_t gram_dma_splits(int64_t npairs, int64_t nchunks) {
+  return std::min<int64_t>(std::max<int64_t>(1, 8192 / npairs), std::max<int64_t>(1, nchunks / 16));
 }
 
-bool gram_dma_eligible(int J, uint64_t L, int elem_size, const void* Y, int prec) {
+// The block products of the register-staged tile pairs, which multiply the
+// blocks past J of a ragged last tile too, over those of this kernel, which
+// leaves them out but takes its chunks slab by slab, so that a last chunk that
+// a short slab does not fill is work as well.  A pair of few blocks takes the
+// time of 24, that of its loads.
+static double gram_dma_gain(int J, uint64_t L, int elem_size) {
+  const int64_t KC = 128 / elem_size, nt = ceil_div(J, 128);
+  double cost = 0.0;
+  for (int64_t a = 0; a < nt; ++a) {
+    const int64_t ba = std::min<int64_t>(8, ceil_div(J - 128 * a, 16));
+    const int64_t bl = std::min<int64_t>(8, ceil_div(J - 128 * (nt - 1), 16));
+    cost += (double)std::max<int64_t>(24, ba * (ba + 1) / 2);
+    if (a < nt - 1) cost += (double)((nt - 2 - a) * 8 * ba) + (double)std::max<int64_t>(24, ba * bl);
+  }
+  const double fill = L == 1 ? 1.0 : (double)L / (double)(ceil_div((int64_t)L, KC) * KC);
+  return 32.0 * (double)(nt * (nt + 1)) * fill / cost;
+}
+
+// FP64, and the reduced forms on unit stride, with 16-byte loads are taken here
+// whatever the shape (FP64 of doubles on row segments at least 1.04 times as fast
+// as the register-staged tile pairs, of floats in slabs that fill three quarters
+// of their chunks, at a gain of 0.83 to 0.91, 0.93 to 0.97).  With 4-byte loads,
+// whose issue the products no longer cover, and for the reduced forms on row
+// segments two things decide:
+//  * the number of items: with few a Gram is one item's chain of 16 chunks long,
+//    which takes 40 to 120 us here, and the other kernel splits finer.  300 rows
+//    of floats in slabs of 65, FP64, us, register-staged against here: 1000
+//    columns (12 items) 38 / 126, 10000 (174) 67 / 101, 30000 (516) 134 / 136, 70000
+//    (1218) 290 / 252;
+//  * the gain, with the lines where the two measured the same.  In us, 200000 or
+//    300000 columns in slabs of L, J at gain:
+//      FP64 of doubles: L = 65 384 at 1.04 1292 / 1407, L = 67 256 at 1.18 656 / 660,
+//        L = 129 384 at 1.15 1283 / 1264, L = 129 256 at 1.26 654 / 611
+//      FP64 of floats:  L = 65 626 at 0.79 3045 / 3469, L = 129 384 at 1.03 1239 / 1214
+//      FP32:    L = 67 257 at 1.22 290 / 368, 16-byte loads 626 at 1.17 1.0 / 1.05
+//      BF16X6:  L = 161 257 at 1.47 290 / 356
+//    and in 400000 columns (ms)
+//      FP32:    L = 447 200 at 1.88 0.45 / 0.35, 336 at 1.48 0.87 / 0.86, 626 at 1.17 2.13 / 2.83
+//      BF16X6:  L = 447 161 at 2.27 0.40 / 0.33, 200 at 1.88 0.42 / 0.38, 336 at 1.48 0.85 / 0.96
+static bool gram_dma_pays(int J, uint64_t L, uint64_t K, int elem_size, bool w16, int prec) {
+  if (w16 && (prec == 0 || L == 1)) return true;
+  const int64_t nt = ceil_div(J, 128), npairs = nt * (nt + 1) / 2;
+  if (gram_dma_splits(npairs, gram_dma_chunks(L, K, elem_size)) * npairs < 1024) return false;
+  const double gain = gram_dma_gain(J, L, elem_size);
+  if (L == 1) return prec != 3 || gain >= 1.2;
+  if (prec == 0) return gain >= (elem_size == 8 ? 1.2 : 1.1);
+  const int64_t KC = 128 / elem_size;
+  return gain >= 1.86 || (prec == 1 && w16 && gain >= 1.2 && 20 * L >= 19 * (uint64_t)(ceil_div((int64_t)L, KC) * KC));
+}
+
+bool gram_dma_eligible(int J, uint64_t L, uint64_t K, int elem_size, const void* Y, int prec) {
   const uint64_t KC = 128 / elem_size;
   return J > 128 && J <= (1 << 20) && reinterpret_cast<uintptr_t>(Y) % elem_size == 0 &&
-         (L == 1 || ((L >= 64 || L % KC == 0) && rows_pay(J, L, elem_size, gram_dma_w16(J, L, elem_size, Y), prec)));
+         (L == 1 || L >= 64 || L % KC == 0) && gram_dma_pays(J, L, K, elem_size, gram_dma_w16(J, L, elem_size, Y), prec);
 }
 
 GramPlan plan_gram_dma(int J, uint64_t L, uint64_t K, int elem_size, int prec) {
   GramPlan p{};
-  const int64_t KC = (L == 1 && elem_size == 8) ? Img<8, 0>::KC : 128 / elem_size;
   p.tile = 128;
-  p.nchunks = (L == 1) ? ceil_div((int64_t)K, KC) : (int64_t)(K / L) * ceil_div((int64_t)L, KC);
+  p.nchunks = gram_dma_chunks(L, K, elem_size);
   p.ntiles = (int)ceil_div(J, 128);
   p.npairs = p.ntiles * (p.ntiles + 1) / 2;
   // about 16 items per workgroup slot (two slots per CU), at least 16 chunks
   // each: items of different speed (diagonal and ragged pairs are faster)
   // then even out over the run; 128 KB of partial blocks per item
-  int64_t nsplit = std::max<int64_t>(1, 8192 / p.npairs);
-  nsplit = std::min<int64_t>(nsplit, std::max<int64_t>(1, p.nchunks / 16));
-  p.cps = ceil_div(p.nchunks, nsplit);
+  p.cps = ceil_div(p.nchunks, gram_dma_splits(p.npairs, p.nchunks));
   p.nsplit = ceil_div(p.nchunks, p.cps);
   p.part_elems = p.nsplit * p.npairs * 64 * 256;
   p.sq_elems = (prec >= 1) ? p.nsplit * p.npairs : 0;
@@ -583,7 +608,7 @@ GramPlan plan_gram_dma(int J, uint64_t L, uint64_t K, int elem_size, int prec) {
 template <typename T>
 hipError_t launch_gram_dma(const T* Y, int J, uint64_t L, uint64_t K, int prec, const GramPlan& p, double* part,
                            double* sq, double* S, double* norm2, hipStream_t stream, hipEvent_t after_main) {
-  if (!gram_dma_eligible(J, L, (int)sizeof(T), Y, prec)) return hipErrorInvalidValue;
+  if (!gram_dma_eligible(J, L, K, (int)sizeof(T), Y, prec)) return hipErrorInvalidValue;
   if (prec != 0 && ((prec != 1 && prec != 3) || sizeof(T) != 4 || sq == nullptr)) return hipErrorInvalidValue;
   DmaParams g{};
   g.Y = reinterpret_cast<const char*>(Y);

@@ -42,7 +42,7 @@ struct GramPlan {
 // 3 BF16X6 products.  Partial blocks in the tile-pair layout of
 // launch_gram_pair_reduce; norm2 (may be null) receives the FP64 sum of
 // squares (trace(S) with FP64 products).
-bool gram_dma_eligible(int J, uint64_t L, int elem_size, const void* Y, int prec);
+bool gram_dma_eligible(int J, uint64_t L, uint64_t K, int elem_size, const void* Y, int prec);
 // prec 0: FP64 products; prec 1: FP32 products, prec 3: BF16X6 products, both
 // of float input (sq: one double per item, p.sq_elems).  Other combinations
 // return hipErrorInvalidValue.

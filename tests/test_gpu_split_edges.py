@@ -222,3 +222,32 @@ def test_slice_transform_large(tk, dims, dt):
     assert torch.equal(y, want)
     back = tk.slice_transform(y, 1, sh, sc, dims=dims, inverse=True)
     assert bool(((back - x).abs() <= (2.0 ** -21 if dt == torch.float32 else 1e-14) * (x.abs() + 4.0)).all())
+
+
+# what the direct-load tile pairs take beside 16-byte loads of FP64 and of unit
+# stride: at least 1024 items, each of 16 chunks of 32 columns (16 of doubles), and
+# a gain past the lines; unaligned columns, row segments and bases, slabs that end
+# inside a chunk, last tiles of a few and of most rows
+@pytest.mark.parametrize("J,L,rest,prec,dt", [
+    (401, 1, 53000, "fp64", torch.float32), (401, 1, 26500, "fp64", torch.float64),
+    (400, 1, 53000, "fp64", torch.float32), (400, 67, 570, "fp64", torch.float32),
+    (400, 67, 335, "fp64", torch.float64), (500, 129, 340, "fp64", torch.float32),
+    (401, 1, 53000, "fp32", torch.float32), (200, 447, 395, "fp32", torch.float32),
+    (672, 256, 99, "fp32", torch.float32), (335, 96, 935, "fp32", torch.float32),
+    (401, 1, 53000, "bf16x6", torch.float32), (200, 447, 395, "bf16x6", torch.float32),
+    (200, 416, 425, "bf16x6", torch.float32),
+])
+def test_tile_pair_gram_many_items(tk, J, L, rest, prec, dt):
+    dims, n = ([J, rest], 0) if L == 1 else ([L, J, rest], 1)
+    tol = {"fp64": 1e-11, "fp32": 2.4e-6, "bf16x6": 1.2e-5}[prec]
+    g = torch.Generator(device="cuda").manual_seed(J + L)
+    buf = torch.randn(J * L * rest + 1, device="cuda", dtype=dt, generator=g)
+    for offset in (0, 1):
+        y = buf[offset:offset + J * L * rest]
+        S, nrm = tk.gram(y, n, prec=prec, dims=dims, with_norm=True)
+        A = y.view(rest, J, L).double().permute(1, 0, 2).reshape(J, rest * L).contiguous()
+        ref = A @ A.t()
+        d = torch.sqrt(torch.outer(ref.diagonal(), ref.diagonal()))
+        assert bool(((S - ref).abs() <= tol * d).all()), offset
+        n2 = float((A * A).sum())
+        assert abs(float(nrm[0]) - n2) <= 1e-12 * n2
