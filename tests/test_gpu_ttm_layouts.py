@@ -308,3 +308,54 @@ def test_ttm_slab_infinity(tk, L, R, J, fp32):
     want[1, :, 3] = float("inf")
     want[R - 1, :, L - 1] = float("-inf")
     assert torch.equal(z, want)
+
+
+def test_ttm_captured_with_a_factor_to_lay_out(tk):
+    """A captured product that would lay its factor out takes no scratch, and
+    replays on new data."""
+    y, M, z, ref, tol = laid_out_operands()
+    side = torch.cuda.Stream()
+    raw_ttm(tk, y, M, z, side)  # leaves an idle block that fits in the pool of this stream
+    torch.cuda.synchronize()
+    assert bool(((z - ref).abs() <= tol).all())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        raw_ttm(tk, y, M, z, side)
+    for s in (1.0, -2.0, 3.0):
+        z.zero_()
+        y.mul_(s)
+        ref, tol = ref * s, tol * abs(s)
+        g.replay()
+        junk = torch.randn(1 << 20, device="cuda").sum()
+        torch.cuda.synchronize()
+        assert bool(((z - ref).abs() <= tol).all())
+        del junk
+
+
+# products past 1e9 flops whose factor is in odd rows: of an odd mode while the
+# eigensolver's workspace, which takes the copy, is used again by the modes after
+# it; of an odd mode at full rank, applied last; and of row ranges that begin at
+# an odd row or have an odd stride, in reconstructions
+@pytest.mark.parametrize("dims,ranks,order", [
+    ([131, 240, 241], [67, 40, 41], [0, 1, 2]),
+    ([240, 131, 241], [40, 67, 41], [1, 2, 0]),
+    ([201, 150, 160], [201, 112, 111], [0, 1, 2]),
+    ([150, 201, 160], [113, 201, 112], [1, 0, 2]),
+])
+def test_laid_out_factors_whole_path(tk, orc, dims, ranks, order):
+    rng = np.random.default_rng(sum(dims))
+    X = rng.standard_normal(int(np.prod(dims)))
+    x = torch.from_numpy(X.reshape(list(reversed(dims)))).cuda()
+    t = tk.sthosvd_ranks(x, ranks, mode_order=order)
+    ref = orc.sthosvd(X, dims, 0.0, order, ranks=ranks)
+    assert t.ranks == list(ref.ranks)
+    np.testing.assert_allclose(t.discarded, ref.discarded, rtol=1e-9, atol=1e-12 * float(np.dot(X, X)))
+    full, _ = orc.reconstruct(ref, [0, 0, 0], dims)
+    got = t.reconstruct().cpu().numpy().reshape(-1)
+    assert np.abs(got - full).max() <= 1e-9 * np.abs(full).max()
+    b, e = [1, 1, 1], dims
+    part, _ = orc.reconstruct(ref, b, e)
+    for o in (None, [2, 1, 0], [1, 2, 0]):
+        got = t.reconstruct(b, e, order=o).cpu().numpy().reshape(-1)
+        assert np.abs(got - part).max() <= 1e-9 * np.abs(part).max()
+    t.free()
