@@ -977,7 +977,7 @@ tucker_status sthosvd_impl(const void* data, tucker_dtype dtype, const int64_t* 
       int64_t L, Rt;
       left_right(cur, N, n, L, Rt);
       if (L > 1 && L * Rt < (int64_t(1) << 32) &&
-          tk::ttm_dma_eligible((int)J, (uint64_t)L, (uint64_t)(L * Rt), (int)Rw, mk, mj, 8, Y, Mu)) {
+          tk::ttm_dma_eligible((int)J, (uint64_t)(L * Rt), (int)Rw, mk, mj, 8, Y, Mu)) {
         rm.Lp = 1;
         for (int k = 0; k < pad; ++k) rm.Lp *= cur[k];
         rm.Pp = cur[pad];
@@ -1432,7 +1432,7 @@ tucker_status reconstruct_impl(const tucker_t* t, const tucker_op* ops, const in
       left_right(pc, N, n, L, Rt);
       // (the core and every intermediate are 16-byte aligned allocations)
       if (L * Rt < (int64_t(1) << 32) &&
-          tk::ttm_dma_eligible((int)pc[n], (uint64_t)L, (uint64_t)(L * Rt), (int)K[n], msk[n], msj[n], 8, t->core,
+          tk::ttm_dma_eligible((int)pc[n], (uint64_t)(L * Rt), (int)K[n], msk[n], msj[n], 8, t->core,
                                M[n])) {
         zpad_step = s - 1;
         const int64_t J0 = cur[0];

@@ -101,8 +101,10 @@ constexpr int kRegMaxJ = 192;
 // reflector() unscales beta and scale (tau is scale-free), as LAPACK's
 // reflector generator does.  Every step waits for these scalars: the square root,
 // its reciprocal and 1 / (alpha - beta) come from the hardware estimates, refined
-// to the last place, with one correction each for beta and tau (55 against 57 us
-// for 64 rows with the library's square root and two divisions).
+// to the last place by Goldschmidt's iteration (the root and half its reciprocal
+// together) and Newton's (the reciprocal), with one correction each for beta and
+// tau (55 against 57 us for 64 rows with the library's square root and two
+// divisions).
 constexpr double kTinyNorm2 = 0x1p-900;
 constexpr double kRowScale = 0x1p+600;
 __device__ __forceinline__ bool row_is_tiny(double alpha, double sigma) {

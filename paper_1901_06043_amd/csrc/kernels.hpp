@@ -98,7 +98,7 @@ __global__ void sum_fixed_kernel(const double* __restrict__ x, int64_t n, double
 // columns (msk = 1) and even stride, 16-byte aligned; any Y and output of
 // float or double, but float Y of more than 32 rows only from the number of
 // tiles on where it is the faster.  launch_ttm uses it when eligible.
-bool ttm_dma_eligible(int J, uint64_t L, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
+bool ttm_dma_eligible(int J, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
                       const void* M);
 // True where only the layout of M stands in the way: a copy P (K x ld, rows
 // contiguous, ld >= J even, 16-byte aligned) made by launch_pack_factor is

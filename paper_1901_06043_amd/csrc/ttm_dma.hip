@@ -120,7 +120,7 @@ __device__ __forceinline__ void loader_init(Loader<TY, ORI, MF, WY>& ld, const T
   };
   if constexpr (WY == 16 && ORI == 0) {
     // the lane's rows are the same for all of the wave's instructions (the
-    // swizzle of j = w + 4 n, or of the j that an instruction of floats
+    // swizzle of j = w + 8 n, or of the j that an instruction of floats
     // covers, depends on the wave and lane only)
     int r, j;
     C::IY::unit_of(wave, lane, r, j);
@@ -473,9 +473,8 @@ static int64_t ttm_dma_tiles(int K, uint64_t cols) {
   return ceil_div(ceil_div(K, 16), 8) * ceil_div((int64_t)cols, 128);
 }
 
-bool ttm_dma_eligible(int J, uint64_t L, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
+bool ttm_dma_eligible(int J, uint64_t cols, int K, int64_t msk, int64_t msj, int ysize, const void* Y,
                       const void* M) {
-  (void)L;
   if (K <= 64 || J < 16 || cols == 0) return false;
   if (ysize == 4 && J > 2 * kJC && ttm_dma_tiles(K, cols) <= kTDFew) return false;
   return ttm_dma_m16(J, K, msk, msj, ysize, M) && reinterpret_cast<uintptr_t>(Y) % ysize == 0;
@@ -524,7 +523,7 @@ hipError_t launch_pack_factor(const double* M, int64_t msk, int64_t msj, int K, 
 template <typename TY, typename TZ>
 hipError_t launch_ttm_dma(const TY* Y, int J, uint64_t L, uint64_t cols, const double* M, int64_t msk, int64_t msj,
                           int K, TZ* Z, hipStream_t stream, const TtmOutRemap& rm) {
-  if (!ttm_dma_eligible(J, L, cols, K, msk, msj, (int)sizeof(TY), Y, M) || cols >= (uint64_t(1) << 32))
+  if (!ttm_dma_eligible(J, cols, K, msk, msj, (int)sizeof(TY), Y, M) || cols >= (uint64_t(1) << 32))
     return hipErrorInvalidValue;
   const bool remap = rm.Pp != rm.Rp;
   if (remap && (L == 1 || rm.Lp < 1 || rm.Rp < 1 || rm.Rp > rm.Pp + 1 || (int64_t)L % (rm.Lp * rm.Pp) != 0))
