@@ -250,6 +250,7 @@ SLABS = [
     (1024, 257, 4, 64), (100, 3000, 7, 2), (202, 1299, 12, 51),
     (64, 8193, 17, 16), (66, 7945, 31, 32), (96, 5462, 32, 33), (1000, 525, 20, 50), (200, 2622, 32, 63),
     (66, 7945, 17, 64), (80, 8300, 24, 5), (64, 8193, 32, 64),
+    (64, 4097, 8, 32), (64, 4097, 11, 48), (128, 2049, 17, 32),
 ]
 
 
