@@ -19,8 +19,8 @@
 // or, with 4-byte loads, four in two.
 // J^2 K flops over the time, before and after: FP64 672x448x33x64 doubles,
 // mode 0: 46.7 -> 58 TF, mode 1 of 448x672x33x64: 45.6 -> 55 TF (FP64 MFMA
-// bound, with 4 TB/s of tile reads beyond L2 close behind); FP32 mode 0 of
-// 672x448x33x64: 52 -> 83 TF; 161x161x160x11x25 (unaligned columns, on the
+// bound, 71 to 79% busy, with 3.4 TB/s of tile reads beyond L2 close behind);
+// FP32 mode 0 of 672x448x33x64: 52 -> 83 TF; 161x161x160x11x25 (unaligned columns, on the
 // register-staged kernel before): FP32 20.6 -> 49, BF16X6 15.9 -> 46 TF.
 // Blocks of rows at or beyond J are skipped, so a ragged last tile costs only
 // its rows.  About 8192 items: the faster diagonal and ragged items then even
